@@ -399,11 +399,8 @@ static void launch_fp6_t(const Fp6GemmArgs& a, const Fp6Plan& p, hipStream_t st)
     launch_fp6_tile<256, AC, BSIGNED>(a, grid, st);
   else
     launch_fp6_tile<128, AC, BSIGNED>(a, grid, st);
-  if (p.splits > 1) {
-    const int64_t MN = a.M * a.N;
-    hipLaunchKernelGGL((splitk_reduce_kernel<AC, 1, BSIGNED>), dim3((unsigned)((MN + 63) / 64)), dim3(256), 0, st,
-                       a.partial, p.splits, MN, a.alpha, a.bscale, a.C);
-  }
+  if (p.splits > 1)
+    launch_split_reduce(a.partial, p.splits, a.M * a.N, EpilogueScale<AC, 1, BSIGNED>{a.alpha, a.bscale}, a.C, st);
 }
 
 hipError_t launch_gemm_luq_int4_fp6(const uint8_t* A, const float* alpha, const uint8_t* B, const float* bscale,

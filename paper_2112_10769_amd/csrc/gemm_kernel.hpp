@@ -11,9 +11,8 @@
 // Carrier: v_mfma_i32_32x32x32_i8 with exact int32 accumulation.  Codes are
 // expanded from nibbles to int8 once per workgroup tile, on the way from
 // global memory into LDS:
-//   LUQ  : a byte LUT (v_perm_b32) maps the exponent field e to 2^(e-1) (or
-//          0), then bytes whose sign bit is set are negated with a SWAR
-//          xor/add.  Two SMP planes are expanded to excess-64 bytes and
+//   LUQ  : two byte lookups (v_perm_b32) and an xor per four codes
+//          (luq_value4).  Two SMP planes are expanded to excess-64 bytes and
 //          summed with one word add (|sum| <= 64, no carries).
 //   INT4 : the nibble is moved to the top of its byte, giving 16*q (signed,
 //          two's complement) or 8*q (unsigned) with no further work; the
@@ -48,7 +47,6 @@ constexpr int kBufferFlags = 0x00020000;
 // A buffer offset beyond any operand's range: such loads return zeros.
 constexpr int kOutOfRange = 0x7FFFFFF0;
 
-constexpr int kGemmThreads = 256;
 constexpr int kKAlign = 128;            // k-chunk granularity of a split
 // int32-exact reduction lengths: |A| <= 64 (LUQ) or 120 (INT4 as 16q / 8q),
 // |B| <= 120: 2^18 * 7680 < 2^31 and 2^17 * 14400 < 2^31
@@ -57,23 +55,26 @@ constexpr int64_t kMaxExactKInt4 = 1 << 17;
 
 // ---- nibble -> int8 expansion ------------------------------------------------
 
+// One LUQ code n = (sign, e) per selector byte -> its int8 value, by two byte
+// lookups whose out-of-table selectors cancel.  v_perm_b32 gives table byte n
+// for a selector below 8, the sign mask of table byte 1, 3, 5 or 7 for 8..11, 0
+// for 12 and 0xFF above.  A positive code reads its value from the first table
+// and a constant f(n) from the second (selector n ^ 8), a negative one the
+// reverse; with f(n) and its counterpart folded into the table entries, the xor
+// of the two lookups is the value: first table {-, 1, 2, 4, 8, ~16, ~32, ~64},
+// second {-, -1, ~(-2), ~(-4), -8, ~(-16), ~(-32), ~(-64)}, the entries for code
+// 0 chosen so that it gives 0.  Code 8 (a negative zero) does not occur.
+// 11 VALU per 8 codes against 14 for a magnitude lookup negated under a sign
+// mask (MLP dX, alone: 368 -> 344 us together with the deeper prefetch it lets
+// fit the registers).
+__device__ __forceinline__ uint32_t luq_value4(uint32_t n) {
+  return __builtin_amdgcn_perm(0xBFDFEF08u, 0x040201FFu, n) ^
+         __builtin_amdgcn_perm(0x3F1F0FF8u, 0x0301FF00u, n ^ 0x08080808u);
+}
+
 __device__ __forceinline__ void expand_luq(uint32_t x, uint32_t& lo, uint32_t& hi) {
-  // bytes 0..7 of the table: 0, 1, 2, 4, 8, 16, 32, 64 (indexed by field e)
-  const uint32_t t_lo = 0x04020100u, t_hi = 0x40201008u;
-  const uint32_t m_lo = __builtin_amdgcn_perm(t_hi, t_lo, x & 0x07070707u);
-  const uint32_t m_hi = __builtin_amdgcn_perm(t_hi, t_lo, (x >> 4) & 0x07070707u);
-  // byte masks of the negative elements: v_perm_b32 selectors 8..11 copy
-  // bit 7 of bytes 1 and 3 of either source into a whole byte, so with the
-  // sources (y << 8, y) selector bytes (10, 8, 11, 9) give byte i = bit 7 of
-  // byte i of y; y = x for the odd-k nibbles, x << 4 for the even-k ones
-  constexpr uint32_t kSignSel = 0x090B080Au;
-  const uint32_t y = x << 4;
-  const uint32_t k_lo = __builtin_amdgcn_perm(y << 8, y, kSignSel);
-  const uint32_t k_hi = __builtin_amdgcn_perm(x << 8, x, kSignSel);
-  // negation = (m ^ 0xFF) + 1, which never carries out of a byte because
-  // m >= 1 wherever the sign is set
-  lo = (m_lo ^ k_lo) + (k_lo & 0x01010101u);
-  hi = (m_hi ^ k_hi) + (k_hi & 0x01010101u);
+  lo = luq_value4(x & 0x0F0F0F0Fu);
+  hi = luq_value4((x >> 4) & 0x0F0F0F0Fu);
 }
 
 // SMP operand (two LUQ planes, R <= 5 so every value is in [-32, 32]): each
@@ -118,13 +119,14 @@ struct GemmArgs {
 };
 
 // Block -> output tile.  Blocks are dispatched round-robin over the 8 XCDs
-// (each with its own L2), so when the tile count allows, consecutive runs of
-// tiles are given to one XCD; within that run tiles are visited in groups of
+// (each with its own L2), so consecutive runs of tiles are given to one XCD;
+// within that run tiles are visited in groups of
 // 8 tile-rows so that the A rows and B rows in flight are shared.
 __device__ __forceinline__ void tile_coords(int bid, int ntm, int ntn, int& tm, int& tn) {
   const int total = ntm * ntn;
-  int L = bid;
-  if ((total & 7) == 0) L = (bid & 7) * (total >> 3) + (bid >> 3);
+  // XCD x takes a run of total / 8 tiles, the first total % 8 XCDs one more
+  const int xcd = bid & 7, q = total >> 3, r = total & 7;
+  const int L = xcd * q + min(xcd, r) + (bid >> 3);
   constexpr int G = 8;
   const int per_group = G * ntn;
   const int first_m = (L / per_group) * G;
@@ -145,304 +147,43 @@ __device__ __forceinline__ float epilogue_scale(float alpha, float bscale) {
   return sc;
 }
 
-// ---- the tile kernel ----------------------------------------------------------
+// ---- the tile kernel: A through LDS, the B operand in registers ----------------
 //
-// 256 threads = 2 x 2 waves; a wave owns a (BM/2) x (BN/2) block of C as
-// (BM/64) x (BN/64) tiles of the 32x32 MFMA.  Per k-stage of BK (64 or 128):
-//   - the packed tile for stage t+2 is loaded into registers,
-//   - stage t is multiplied out of LDS buffer t%2,
-//   - stage t+1 (loaded one iteration earlier) is expanded into LDS buffer
-//     (t+1)%2,
-// all in one block of straight-line code, with the expansion and loads cut
-// into one piece per 32-deep k-step and placed after that k-step's MFMAs, so
-// the VALU work issues between MFMAs.  The MFMA takes the B fragment as its
-// first operand, so each lane ends up with 4 consecutive columns of one C row.
+// KG k-groups of WM x WN waves (eight waves, but for the small four-wave tile);
+// a wave owns a (32 TM) x (32 TN) block of C, so a workgroup's tile is
+// BM = 32 WM TM rows by BN = 32 WN TN columns and two or more waves share each
+// SIMD: the expansion, address and LDS work of one overlaps the MFMAs of the
+// others.  The MFMA takes the B fragment as its first operand, so each lane ends
+// up with 4 consecutive columns of one C row.  Operands are read through buffer
+// descriptors whose range is the operand itself: rows past M (or N) fall
+// outside the range, and with FULLK false a chunk past the end of the split's k
+// range is given an offset outside it, so both read as zeros without a branch.
+// FULLK: K is a multiple of BK, so every stage of a split lies inside the
+// operands' rows; stages past the end of the split are never multiplied.
 //
-// FULLK: K is a multiple of kKAlign, so every stage of a split lies inside
-// the operands' rows and no chunk needs a per-lane range check; stages past
-// the end of the split are then never multiplied.  Otherwise chunks past
-// the split's end read as zeros and the loop may multiply one zero stage.
-// The 64-deep variant keeps three waves per SIMD.
+// AC is the A operand's code type: LUQ (NS planes), INT4 (the forward product,
+// NS = 1), expanded like B, or the int8 sums of two LUQ samples (NS = 1): 32
+// bytes per 32-deep chunk, whose bytes only need the even / odd k split of the
+// nibble expansions (two byte permutes per 8 values).
 //
-// AC is the A operand's code type: LUQ (NS planes), INT4 (the forward
-// product, NS = 1), expanded like B, or the int8 sums of two LUQ samples
-// (NS = 1): 32 bytes per 32-deep chunk, whose bytes only need the even / odd
-// k split of the nibble expansions (two byte permutes per 8 values).
-template <int BM, int BN, int BK, int AC, int NS, bool BSIGNED, bool FULLK>
-__global__ __launch_bounds__(kGemmThreads, BK == 64 ? 3 : 1) void gemm_luq_int4_kernel(GemmArgs a) {
-  static_assert(BM % 64 == 0 && BN % 64 == 0, "wave tiles are multiples of 32");
-  static_assert(BK == 64 || BK == 128, "k per stage");
-  constexpr int kBK = BK;
-  constexpr int kPitch = BK + 16;                      // LDS row pitch in bytes
-  constexpr int KC = BK / 32;                          // 16-byte chunks per row and stage
-  constexpr int TM = BM / 64, TN = BN / 64;            // 32x32 MFMA tiles per wave
-  constexpr int ACH = BM * KC / kGemmThreads;          // 16-byte A chunks per thread and stage
-  constexpr int BCH = BN * KC / kGemmThreads;
-  static_assert(ACH >= 1 && BCH >= 1, "tile too small for the block");
-  constexpr int STAGE = (BM + BN) * kPitch;            // bytes of one LDS stage
-  __shared__ __attribute__((aligned(16))) uint8_t lds[2 * STAGE];
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-  int tm, tn;
-  tile_coords(blockIdx.x, a.tiles_m, a.tiles_n, tm, tn);
-  const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
-  const int64_t kbeg = (int64_t)blockIdx.y * a.k_chunk;
-  const int64_t kend = min(kbeg + a.k_chunk, a.K);
-  const int nkt = (int)((kend - kbeg + kBK - 1) / kBK);
-  constexpr bool kI8 = AC == kAcSum2;
-  constexpr int NA = kI8 ? 2 : NS;          // 16-byte A registers per chunk
-  const int64_t ld = a.K >> 1;              // bytes per B row (and per nibble A row)
-  const int64_t lda = kI8 ? a.K : ld;       // bytes per A row
-
-  // Operands are read through buffer descriptors whose range is the operand
-  // itself: rows past M (or N) fall outside the range, and a chunk past the
-  // end of this split's k range is given an offset outside it, so both read
-  // as zeros without a branch.
-  __amdgpu_buffer_rsrc_t rsa[NS];
-#pragma unroll
-  for (int s = 0; s < NS; ++s)
-    rsa[s] = __builtin_amdgcn_make_buffer_rsrc((void*)(a.A + s * a.a_plane), (short)0,
-                                               (int)(a.M * lda), kBufferFlags);
-  const __amdgpu_buffer_rsrc_t rsb =
-      __builtin_amdgcn_make_buffer_rsrc((void*)a.B, (short)0, (int)(a.N * ld), kBufferFlags);
-  int offa[ACH], kca[ACH], offb[BCH], kcb[BCH];
-#pragma unroll
-  for (int i = 0; i < ACH; ++i) {
-    const int c = tid + i * kGemmThreads, row = c / KC, kc = c % KC;
-    kca[i] = kc * 32;
-    offa[i] = kI8 ? (int)((m0 + row) * lda + kbeg + kc * 32) : (int)((m0 + row) * ld + (kbeg >> 1) + kc * 16);
-  }
-#pragma unroll
-  for (int i = 0; i < BCH; ++i) {
-    const int c = tid + i * kGemmThreads, row = c / KC, kc = c % KC;
-    kcb[i] = kc * 32;
-    offb[i] = (int)((n0 + row) * ld + (kbeg >> 1) + kc * 16);
-  }
-
-  struct Regs {
-    v4u a[NA][ACH];
-    v4u b[BCH];
-  };
-  // Work of one stage is split into KS pieces, one per 32-deep k-step: piece
-  // kk covers the A and B chunks i with i % KS == kk.
-  constexpr int KS = kBK / 32;
-  auto load_piece = [&](Regs& r, int t, int kk) {
-    const int64_t k0 = kbeg + (int64_t)t * kBK;
-#pragma unroll
-    for (int i = 0; i < ACH; ++i) {
-      if (i % KS != kk) continue;
-      const bool in = FULLK || (k0 + kca[i]) < kend;
-      if constexpr (kI8) {
-        const int off = in ? offa[i] + t * kBK : kOutOfRange;
-        r.a[0][i] = __builtin_amdgcn_raw_buffer_load_b128(rsa[0], off, 0, 0);
-        r.a[1][i] = __builtin_amdgcn_raw_buffer_load_b128(rsa[0], in ? off + 16 : kOutOfRange, 0, 0);
-      } else {
-        const int off = in ? offa[i] + t * (kBK / 2) : kOutOfRange;
-#pragma unroll
-        for (int s = 0; s < NS; ++s) r.a[s][i] = __builtin_amdgcn_raw_buffer_load_b128(rsa[s], off, 0, 0);
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < BCH; ++i) {
-      if (i % KS != kk) continue;
-      const int off = FULLK || (k0 + kcb[i]) < kend ? offb[i] + t * (kBK / 2) : kOutOfRange;
-      r.b[i] = __builtin_amdgcn_raw_buffer_load_b128(rsb, off, 0, 0);
-    }
-  };
-  auto expand_piece = [&](const Regs& r, int buf, int kk) {
-    uint8_t* As = lds + buf * STAGE;
-    uint8_t* Bs = As + BM * kPitch;
-#pragma unroll
-    for (int i = 0; i < ACH; ++i) {
-      if (i % KS != kk) continue;
-      const int c = tid + i * kGemmThreads, row = c / KC, kc = c % KC;
-      uint32_t w[8];
-      const uint32_t x0[4] = {r.a[0][i][0], r.a[0][i][1], r.a[0][i][2], r.a[0][i][3]};
-      if constexpr (kI8) {
-        // bytes of k = 8d .. 8d+7 are words 2d, 2d+1 of the 32-byte chunk
-        const uint32_t x[8] = {x0[0], x0[1], x0[2], x0[3], r.a[1][i][0], r.a[1][i][1], r.a[1][i][2], r.a[1][i][3]};
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-          w[2 * d] = __builtin_amdgcn_perm(x[2 * d + 1], x[2 * d], 0x06040200u);      // k even
-          w[2 * d + 1] = __builtin_amdgcn_perm(x[2 * d + 1], x[2 * d], 0x07050301u);  // k odd
-        }
-      } else if constexpr (AC != kAcLuq) {
-#pragma unroll
-        for (int d = 0; d < 4; ++d) expand_int4<AC == kAcInt4S>(x0[d], w[2 * d], w[2 * d + 1]);
-      } else if constexpr (NS == 1) {
-#pragma unroll
-        for (int d = 0; d < 4; ++d) expand_luq(x0[d], w[2 * d], w[2 * d + 1]);
-      } else {
-        const uint32_t x1[4] = {r.a[1][i][0], r.a[1][i][1], r.a[1][i][2], r.a[1][i][3]};
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-          uint32_t l0, h0, l1, h1;
-          expand_luq_excess64(x0[d], l0, h0);
-          expand_luq_excess64(x1[d], l1, h1);
-          w[2 * d] = (l0 + l1) ^ 0x80808080u;
-          w[2 * d + 1] = (h0 + h1) ^ 0x80808080u;
-        }
-      }
-      uint4* dst = reinterpret_cast<uint4*>(As + row * kPitch + kc * 32);
-      dst[0] = make_uint4(w[0], w[1], w[2], w[3]);
-      dst[1] = make_uint4(w[4], w[5], w[6], w[7]);
-    }
-#pragma unroll
-    for (int i = 0; i < BCH; ++i) {
-      if (i % KS != kk) continue;
-      const int c = tid + i * kGemmThreads, row = c / KC, kc = c % KC;
-      uint32_t w[8];
-      const uint32_t x0[4] = {r.b[i][0], r.b[i][1], r.b[i][2], r.b[i][3]};
-#pragma unroll
-      for (int d = 0; d < 4; ++d) expand_int4<BSIGNED>(x0[d], w[2 * d], w[2 * d + 1]);
-      uint4* dst = reinterpret_cast<uint4*>(Bs + row * kPitch + kc * 32);
-      dst[0] = make_uint4(w[0], w[1], w[2], w[3]);
-      dst[1] = make_uint4(w[4], w[5], w[6], w[7]);
-    }
-  };
-
-  v16i acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j) acc[i][j] = v16i{};
-
-  // 32x32x32 MFMA operands: lane l supplies row l%32 and 16 consecutive k
-  // (positions 16*(l/32) .. +15 of the 32-k step) of its fragment.
-  struct Frags {
-    v4i a[TM], b[TN];
-  };
-  auto read_frags = [&](int buf, int kk, Frags& f) {
-    const uint8_t* As = lds + buf * STAGE;
-    const uint8_t* as = As + (wm * (BM / 2) + (lane & 31)) * kPitch + (lane >> 5) * 16 + kk * 32;
-    const uint8_t* bs = As + BM * kPitch + (wn * (BN / 2) + (lane & 31)) * kPitch + (lane >> 5) * 16 + kk * 32;
-#pragma unroll
-    for (int i = 0; i < TM; ++i) f.a[i] = *reinterpret_cast<const v4i*>(as + i * 32 * kPitch);
-#pragma unroll
-    for (int j = 0; j < TN; ++j) f.b[j] = *reinterpret_cast<const v4i*>(bs + j * 32 * kPitch);
-  };
-  auto mfmas = [&](const Frags& f) {
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(f.b[j], f.a[i], acc[i][j], 0, 0, 0);
-  };
-
-  // One pipeline step, straight-line code between barriers: for each k-step
-  // of stage `cb` (in LDS), the fragments of the next k-step are read ahead,
-  // the MFMAs of this k-step issue, and one piece of the next stage (the
-  // registers `r`) is expanded into the other buffer, after which that
-  // piece's registers are reloaded from stage `tload` into `rl`.  Source
-  // order interleaves the expansion work with the MFMAs.
-  auto step = [&](int cb, const Regs& r, Regs& rl, int tload) {
-    Frags f[2];
-    read_frags(cb, 0, f[0]);
-#pragma unroll
-    for (int kk = 0; kk < KS; ++kk) {
-      if (kk + 1 < KS) read_frags(cb, kk + 1, f[(kk + 1) & 1]);
-      mfmas(f[kk & 1]);
-      expand_piece(r, cb ^ 1, kk);
-      load_piece(rl, tload, kk);
-    }
-    __syncthreads();
-  };
-
-  Regs r0, r1;
-#pragma unroll
-  for (int kk = 0; kk < KS; ++kk) load_piece(r0, 0, kk);
-#pragma unroll
-  for (int kk = 0; kk < KS; ++kk) load_piece(r1, 1, kk);
-#pragma unroll
-  for (int kk = 0; kk < KS; ++kk) expand_piece(r0, 0, kk);
-  __syncthreads();
-#pragma unroll
-  for (int kk = 0; kk < KS; ++kk) load_piece(r0, 2, kk);
-  int t = 0;
-  for (; t + 2 <= nkt; t += 2) {
-    step(0, r1, r1, t + 3);   // multiply t, expand t+1 (r1), then reuse r1 for t+3
-    step(1, r0, r0, t + 4);   // multiply t+1, expand t+2 (r0), then reuse r0 for t+4
-  }
-  // an odd stage count leaves stage t in buffer 0 (with FULLK the stage
-  // expanded beside it may hold another split's codes; it is not multiplied)
-  if (t < nkt) step(0, r1, r1, t + 3);
-
-  // Epilogue through LDS.  In MFMA tile (i, j), lane l holds row l%32 and, in
-  // registers 4q..4q+3, the 4 consecutive columns 8q + 4*(l/32) + 0..3 (the
-  // swapped operands).  Each wave stages 32 rows of its block at a time as a
-  // row-major slab in its own part of the (now idle) stage buffers, then
-  // stores whole row segments: WN/4 consecutive lanes cover one row of the
-  // wave's block, so a store instruction writes 64*16/WN-row runs of
-  // contiguous 16-byte chunks.  C gets the scaled fp32 values, the split-K
-  // workspace the raw int32 sums.
-  constexpr int WM = BM / 2, WN = BN / 2;
-  constexpr int EP = WN + 4;      // slab row pitch in 32-bit words
-  constexpr int LPR = WN / 4;     // lanes per row in the store phase
-  constexpr int RPI = 64 / LPR;   // rows per store instruction (lanes past RPI * LPR idle)
-  static_assert(4 * 32 * EP * 4 <= 2 * STAGE, "epilogue slabs fit in the stage buffers");
-  static_assert(WM % 32 == 0 && LPR <= 64 && 32 % RPI == 0, "slab shape");
-  uint32_t* E = reinterpret_cast<uint32_t*>(lds) + wave * 32 * EP;
-  const bool part = a.partial != nullptr;
-  const float sc = part ? 0.0f : epilogue_scale<AC, NS, BSIGNED>(*a.alpha, *a.bscale);
-  uint32_t* out = part ? reinterpret_cast<uint32_t*>(a.partial + (int64_t)blockIdx.y * a.M * a.N)
-                       : reinterpret_cast<uint32_t*>(a.C);
-  const int64_t rbase = m0 + wm * WM, cbase = n0 + wn * WN;
-  const int srow = lane / LPR, scol = (lane % LPR) * 4;
-  const bool sact = lane < RPI * LPR;
-  __syncthreads();  // every wave is done with the stage buffers
-#pragma unroll
-  for (int i = 0; i < TM; ++i) {
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        v4u v;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int32_t x = acc[i][j][4 * q + r];
-          v[r] = part ? (uint32_t)x : __float_as_uint(__fmul_rn((float)x, sc));
-        }
-        *reinterpret_cast<v4u*>(E + (lane & 31) * EP + j * 32 + 8 * q + 4 * (lane >> 5)) = v;
-      }
-    __syncthreads();
-#pragma unroll
-    for (int rr = 0; rr < 32; rr += RPI) {
-      const int64_t row = rbase + i * 32 + rr + srow;
-      const int64_t col = cbase + scol;
-      if (sact && row < a.M) {
-        const v4u v = *reinterpret_cast<const v4u*>(E + (rr + srow) * EP + scol);
-        uint32_t* dst = out + row * a.N + col;
-        if (a.vec && col + 3 < a.N) {
-          *reinterpret_cast<v4u*>(dst) = v;
-        } else {
-#pragma unroll
-          for (int r = 0; r < 4; ++r)
-            if (col + r < a.N) dst[r] = v[r];
-        }
-      }
-    }
-    __syncthreads();  // the slab is rewritten by the next i
-  }
-}
-
-// ---- the 256 x 256 tile: eight waves, the B operand in registers ---------------
+// Only A passes through LDS, expanded
+// to int8 once per workgroup (the LUQ expansion is the costly one, and LDS
+// stores run at a quarter of the LDS read rate).  Each wave loads the nibbles
+// of its own 32 TN B rows straight into registers (the waves of the other row
+// blocks load the same rows) and expands every fragment just before its MFMAs,
+// which is a shift and a mask per word.
 //
-// 512 threads = 2 x 4 waves; a wave owns a 128 x 64 block of C (4 x 2 tiles of
-// the 32x32 MFMA), so two waves share each SIMD and the expansion, address and
-// LDS work of one overlaps the MFMAs of the other.  Only A passes through LDS,
-// expanded to int8 once per workgroup (the LUQ expansion is the costly one,
-// and LDS stores run at a quarter of the LDS read rate).  Each wave loads the
-// nibbles of its own 64 B rows straight into registers (the wave of the other
-// row half loads the same rows) and expands every fragment just before its
-// MFMAs, which is a shift and a mask per word.
+// With KG > 1 the k-groups share the tile and take 128 k each of a stage of
+// 128 KG: a small tile still feeds eight waves, each with long contiguous B
+// segments in flight, and the groups' int32 sums are added through LDS in the
+// epilogue instead of through memory.
 //
-// k order: a 128-deep stage is 64 nibble bytes of every row.  At k-step kk,
-// lane half h = lane/32 supplies the k of nibble bytes 32h + 8kk .. +7 of the
-// stage, for both operands, so a lane's B nibbles of a whole stage are one
-// contiguous 32-byte segment.  The products summed are the same, in another
-// order.  A sits in LDS as 8 slots of 16 expanded bytes per row, slot 2kk + h
-// holding those k.
+// k order: a 128-deep group stage is 64 nibble bytes of every row.  At k-step
+// kk, lane half h = lane/32 supplies the k of nibble bytes 32h + 8kk .. +7 of
+// the group's 64, for both operands, so a lane's B nibbles of a whole stage
+// are one contiguous 32-byte segment.  The products summed are the same, in
+// another order.  A sits in LDS as 8 KG slots of 16 expanded bytes per row,
+// slot 8g + 2kk + h holding those k.
 //
 // Pipeline (one barrier per stage): stage t is multiplied from LDS buffer t%2
 // with B registers set t%2, while the A codes of stage t+1 are expanded into
@@ -457,26 +198,46 @@ __global__ __launch_bounds__(kGemmThreads, BK == 64 ? 3 : 1) void gemm_luq_int4_
 //   3: as 2 across the stage boundary as well (the next stage's first B
 //      fragments at the last k-step), with the B reload one k-step earlier.
 // Every mode sums the same products; the launcher picks the deepest mode that
-// fits the 256 registers of two waves per SIMD for the operand kinds.
-constexpr int kW8Threads = 512;
+// fits the register budget for the operand kinds.
 
-template <int AC, int NS, bool BSIGNED, bool FULLK, int PF>
-__global__ __launch_bounds__(kW8Threads, 1) void gemm_w8_kernel(GemmArgs a) {
-  constexpr int BM = 256, kBK = 128, kThr = kW8Threads;
-  constexpr int kPitch = kBK + 16;        // A row: 8 slots of 16 bytes, 16 bytes of pad
+// Shape of a tile; OCC = waves per SIMD its registers must allow (512 / OCC
+// registers a wave: two workgroups of the smaller tiles fit a CU).
+template <int WM_, int WN_, int KG_, int TM_, int TN_, int OCC_>
+struct GemmShape {
+  static constexpr int WM = WM_, WN = WN_, KG = KG_, TM = TM_, TN = TN_, OCC = OCC_;
+  static constexpr int BM = 32 * WM * TM, BN = 32 * WN * TN, BK = 128 * KG;
+  static constexpr int NW = WM * WN * KG, THREADS = 64 * NW;
+};
+using Tile256x256 = GemmShape<2, 4, 1, 4, 2, 1>;
+using Tile128x256 = GemmShape<2, 4, 1, 2, 2, 2>;
+using Tile128x128 = GemmShape<2, 4, 1, 2, 1, 4>;
+using Tile64x128 = GemmShape<1, 4, 2, 2, 1, 4>;
+using Tile64x64 = GemmShape<1, 2, 4, 2, 1, 4>;
+using Tile32x64 = GemmShape<1, 2, 4, 1, 1, 4>;
+using Tile32x32 = GemmShape<1, 1, 8, 1, 1, 4>;
+using Tile64x64k1 = GemmShape<2, 2, 1, 1, 1, 4>;
+
+template <int AC, int NS, bool BSIGNED, bool FULLK, int PF, typename S>
+__global__ __launch_bounds__(S::THREADS, S::OCC) void gemm_tile_kernel(GemmArgs a) {
+  constexpr int BM = S::BM, kBK = S::BK, kThr = S::THREADS, KG = S::KG;
+  constexpr int kPitch = kBK + 16;        // A row: 8 KG slots of 16 bytes, 16 bytes of pad
   constexpr int STAGE = BM * kPitch;
-  constexpr int TM = 4, TN = 2;           // 32x32 tiles per wave
-  constexpr int ACH = BM * 4 / kThr;      // 16-byte A chunks per thread and stage
+  constexpr int TM = S::TM, TN = S::TN;   // 32x32 tiles per wave
+  constexpr int KC = kBK / 32;            // 16-byte A chunks per row and stage
+  constexpr int ACH = BM * KC / kThr;     // A chunks per thread and stage
   constexpr bool kI8 = AC == kAcSum2;
   constexpr int NA = kI8 ? 2 : NS;
-  static_assert(ACH == 2, "one A half-chunk per k-step");
-  __shared__ __attribute__((aligned(16))) uint8_t lds[2 * STAGE];
+  static_assert(ACH == 1 || ACH == 2, "at most one A half-chunk per k-step");
+  static_assert(BM * KC % kThr == 0, "every thread loads the same chunks");
+  constexpr int EP = 32 * TN + 4;         // epilogue slab row pitch in 32-bit words
+  constexpr int kSlabs = S::NW * 32 * EP * 4;
+  __shared__ __attribute__((aligned(16))) uint8_t lds[2 * STAGE > kSlabs ? 2 * STAGE : kSlabs];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 2, wn = wave & 3, h = lane >> 5;
+  const int kg = wave / (S::WM * S::WN), wm = (wave / S::WN) % S::WM, wn = wave % S::WN, h = lane >> 5;
   int tm, tn;
   tile_coords(blockIdx.x, a.tiles_m, a.tiles_n, tm, tn);
-  const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * 256;
+  const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * S::BN;
   const int64_t kbeg = (int64_t)blockIdx.y * a.k_chunk;
   const int64_t kend = min(kbeg + a.k_chunk, a.K);
   const int nkt = (int)((kend - kbeg + kBK - 1) / kBK);
@@ -490,20 +251,28 @@ __global__ __launch_bounds__(kW8Threads, 1) void gemm_w8_kernel(GemmArgs a) {
                                                (int)(a.M * lda), kBufferFlags);
   const __amdgpu_buffer_rsrc_t rsb =
       __builtin_amdgcn_make_buffer_rsrc((void*)a.B, (short)0, (int)(a.N * ld), kBufferFlags);
-  // A loader: chunk i of a thread is row c/4, 16 nibble bytes (32 k) at 16*(c%4)
+  // A loader: chunk i of a thread is row c/KC, 16 nibble bytes (32 k) at 16*(c%KC)
   int offa[ACH], kca[ACH], slota[ACH], rowa[ACH];
 #pragma unroll
   for (int i = 0; i < ACH; ++i) {
-    const int c = tid + i * kThr, row = c >> 2, kc = c & 3;
+    const int c = tid + i * kThr, row = c / KC, kc = c % KC;
     kca[i] = kc * 32;
     rowa[i] = row;
-    slota[i] = 4 * (kc & 1) + (kc >> 1);  // slot of the chunk's first half; the second is 2 further
+    // slot of the chunk's first half; the second is 2 further
+    slota[i] = 8 * (kc >> 2) + 4 * (kc & 1) + ((kc >> 1) & 1);
     offa[i] = kI8 ? (int)((m0 + row) * lda + kbeg + kc * 32) : (int)((m0 + row) * ld + (kbeg >> 1) + kc * 16);
   }
-  // B: rows n0 + 64wn + 32j + lane%32, the 32-byte segment 32h of each stage
+  // B loader: load q takes the rows 2i + q of a 32-row block, lane l the
+  // 16-byte chunk kcb of row (l & 30) + q, so that neighbouring lanes read 32
+  // contiguous bytes and an instruction takes 64 bytes from each of 16 rows.
+  // With one row per lane an instruction touched 32 rows, twice, and the
+  // address unit bound the kernel (MLP dX, alone: 400 -> 365 us; a copy that
+  // left the lanes unpaired: 330)
+  const int kcb = (lane & 1) | (h << 1);
   int offb[TN];
 #pragma unroll
-  for (int j = 0; j < TN; ++j) offb[j] = (int)((n0 + wn * 64 + j * 32 + (lane & 31)) * ld + (kbeg >> 1) + h * 32);
+  for (int j = 0; j < TN; ++j)
+    offb[j] = (int)((n0 + (wn * TN + j) * 32 + (lane & 30)) * ld + (kbeg >> 1) + kg * 64 + kcb * 16);
 
   struct ARegs {
     v4u a[NA][ACH];
@@ -525,10 +294,26 @@ __global__ __launch_bounds__(kW8Threads, 1) void gemm_w8_kernel(GemmArgs a) {
     }
   };
   auto load_b = [&](BRegs& r, int t, int q) {
-    const bool in = FULLK || (kbeg + (int64_t)t * kBK + h * 64 + q * 32) < kend;
+    const bool in = FULLK || (kbeg + (int64_t)t * kBK + kg * 128 + kcb * 32) < kend;
 #pragma unroll
     for (int j = 0; j < TN; ++j)
-      r.b[j][q] = __builtin_amdgcn_raw_buffer_load_b128(rsb, in ? offb[j] + t * (kBK / 2) + q * 16 : kOutOfRange, 0, 0);
+      r.b[j][q] =
+          __builtin_amdgcn_raw_buffer_load_b128(rsb, in ? offb[j] + t * (kBK / 2) + q * (int)ld : kOutOfRange, 0, 0);
+  };
+  // dwords 2hf, 2hf + 1 of a loaded set, exchanged within the lane pairs so that
+  // lane l holds row l%32: b[.][q] becomes bytes 32h + 16q .. +15 of its row
+  const bool odd = lane & 1;
+  auto pair_b = [&](BRegs& r, int hf) {
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int d = 2 * hf; d < 2 * hf + 2; ++d) {
+        const uint32_t x = r.b[j][0][d], y = r.b[j][1][d];
+        // what the neighbour lane needs: quad_perm (1, 0, 3, 2)
+        const uint32_t u = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(odd ? x : y), 0xB1, 0xF, 0xF, true);
+        r.b[j][0][d] = odd ? u : x;
+        r.b[j][1][d] = odd ? y : u;
+      }
   };
   // half hf of A chunk i (its k 16hf .. 16hf+15) -> 16 bytes of LDS
   auto expand_a = [&](const ARegs& r, int buf, int i, int hf) {
@@ -565,8 +350,8 @@ __global__ __launch_bounds__(kW8Threads, 1) void gemm_w8_kernel(GemmArgs a) {
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = v16i{};
 
-  // A fragment i of k-step kk: row 128wm + 32i + lane%32, slot 2kk + h
-  const int aoff = (wm * 128 + (lane & 31)) * kPitch + (h << 4);
+  // A fragment i of k-step kk: row 32 (TM wm + i) + lane%32, slot 8 kg + 2kk + h
+  const int aoff = (wm * TM * 32 + (lane & 31)) * kPitch + kg * 128 + (h << 4);
   auto read_a = [&](int buf, int kk, v4i (&fa)[TM]) {
     const uint8_t* as = lds + buf * STAGE + aoff + (kk << 5);
 #pragma unroll
@@ -594,11 +379,13 @@ __global__ __launch_bounds__(kW8Threads, 1) void gemm_w8_kernel(GemmArgs a) {
   };
   // multiply stage t from buffer cb and B set rb while expanding the A codes
   // of stage t+1 (ra) into the other buffer; rbn is the next stage's B set
-  auto step = [&](int cb, ARegs& ra, int ta, BRegs& rb, int tb, const BRegs& rbn) {
+  auto step = [&](int cb, ARegs& ra, int ta, BRegs& rb, int tb, BRegs& rbn) {
     if constexpr (PF >= 1) read_a(cb, 0, fa2[0]);
+    if constexpr (PF != 3) pair_b(rb, 0);
     if constexpr (PF == 2) frag_b(rb, 0, fb2[0]);
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
+      if (kk == (PF >= 2 ? 0 : 1)) pair_b(rb, 1);
       // the first B half-segment and A chunk are consumed: reload them now
       // (the scheduler would otherwise sink the loads to the barrier)
       if (kk == (PF == 3 ? 1 : 2)) {
@@ -625,14 +412,15 @@ __global__ __launch_bounds__(kW8Threads, 1) void gemm_w8_kernel(GemmArgs a) {
           read_a(cb, kk + 1, fa2[(kk + 1) & 1]);
           frag_b(rb, kk + 1, fb2[(kk + 1) & 1]);
         } else if (PF == 3) {
+          pair_b(rbn, 0);
           frag_b(rbn, 0, fb2[0]);
         }
         mma(fa2[kk & 1], fb2[kk & 1]);
       }
-      expand_a(ra, cb ^ 1, kk >> 1, kk & 1);
+      if (kk < 2 * ACH) expand_a(ra, cb ^ 1, kk >> 1, kk & 1);
     }
     load_b(rb, tb, 1);
-    load_a(ra, ta, 1);
+    if constexpr (ACH == 2) load_a(ra, ta, 1);
     __syncthreads();
     // keep the next stage's work below the barrier: hoisted above it, the
     // expansion of registers loaded in this stage would wait for those loads
@@ -645,13 +433,20 @@ __global__ __launch_bounds__(kW8Threads, 1) void gemm_w8_kernel(GemmArgs a) {
   for (int i = 0; i < ACH; ++i) load_a(r0, 0, i);
   load_b(b0, 0, 0);
   load_b(b0, 0, 1);
+  // the order of the loop: the waits at its head, which hold for the entry and
+  // for the back edge, then count the same loads behind the ones they need
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int i = 0; i < ACH; ++i) load_a(r1, 1, i);
   load_b(b1, 1, 0);
   load_b(b1, 1, 1);
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk) expand_a(r0, 0, kk >> 1, kk & 1);
-  if constexpr (PF == 3) frag_b(b0, 0, fb2[0]);
+  for (int kk = 0; kk < 2 * ACH; ++kk) expand_a(r0, 0, kk >> 1, kk & 1);
+  if constexpr (PF == 3) {
+    pair_b(b0, 0);
+    frag_b(b0, 0, fb2[0]);
+  }
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < ACH; ++i) load_a(r0, 2, i);
@@ -662,18 +457,22 @@ __global__ __launch_bounds__(kW8Threads, 1) void gemm_w8_kernel(GemmArgs a) {
   }
   if (t < nkt) step(0, r1, t + 3, b0, t + 2, b1);
 
-  // Epilogue through LDS, as in the four-wave kernel: each wave stages 32 rows
-  // of its 128 x 64 block at a time and stores whole 256-byte row segments.
-  constexpr int WN = 64;
-  constexpr int EP = WN + 4;
-  constexpr int LPR = WN / 4, RPI = 64 / LPR;
-  static_assert(8 * 32 * EP * 4 <= 2 * STAGE, "epilogue slabs fit in the stage buffers");
+  // Epilogue through LDS.  In MFMA tile (i, j), lane l holds row l%32 and, in
+  // registers 4q..4q+3, the 4 consecutive columns 8q + 4*(l/32) + 0..3.  Each
+  // wave stages 32 rows of its block at a time as a row-major slab in its own
+  // part of the (now idle) stage buffers, then stores whole row segments: LPR
+  // consecutive lanes cover one row of the block, RPI rows per instruction.  With
+  // KG > 1 the slabs hold the int32 sums and each k-group's wave stores 32 / KG of
+  // the block's rows, adding the KG slabs of that block.  C gets the scaled fp32
+  // values, the split-K workspace the raw int32 sums.
+  constexpr int LPR = 8 * TN, RPI = 64 / LPR, SR = 32 / KG;
   uint32_t* E = reinterpret_cast<uint32_t*>(lds) + wave * 32 * EP;
+  const uint32_t* E0 = reinterpret_cast<const uint32_t*>(lds) + (wave % (S::WM * S::WN)) * 32 * EP;
   const bool part = a.partial != nullptr;
   const float sc = part ? 0.0f : epilogue_scale<AC, NS, BSIGNED>(*a.alpha, *a.bscale);
   uint32_t* out = part ? reinterpret_cast<uint32_t*>(a.partial + (int64_t)blockIdx.y * a.M * a.N)
                        : reinterpret_cast<uint32_t*>(a.C);
-  const int64_t rbase = m0 + wm * 128, cbase = n0 + wn * WN;
+  const int64_t rbase = m0 + wm * TM * 32, cbase = n0 + wn * TN * 32;
   const int srow = lane / LPR, scol = (lane % LPR) * 4;
   __syncthreads();  // every wave is done with the stage buffers
 #pragma unroll
@@ -686,17 +485,27 @@ __global__ __launch_bounds__(kW8Threads, 1) void gemm_w8_kernel(GemmArgs a) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int32_t x = acc[i][j][4 * q + r];
-          v[r] = part ? (uint32_t)x : __float_as_uint(__fmul_rn((float)x, sc));
+          v[r] = KG > 1 || part ? (uint32_t)x : __float_as_uint(__fmul_rn((float)x, sc));
         }
         *reinterpret_cast<v4u*>(E + (lane & 31) * EP + j * 32 + 8 * q + 4 * (lane >> 5)) = v;
       }
     __syncthreads();
 #pragma unroll
-    for (int rr = 0; rr < 32; rr += RPI) {
-      const int64_t row = rbase + i * 32 + rr + srow;
+    for (int rr = 0; rr < SR; rr += RPI) {
+      const int sr = kg * SR + rr + srow;
+      const int64_t row = rbase + i * 32 + sr;
       const int64_t col = cbase + scol;
-      if (row < a.M) {
-        const v4u v = *reinterpret_cast<const v4u*>(E + (rr + srow) * EP + scol);
+      if (row < a.M && (SR % RPI == 0 || rr + srow < SR)) {
+        v4u v = *reinterpret_cast<const v4u*>(E0 + sr * EP + scol);
+        if constexpr (KG > 1) {
+#pragma unroll
+          for (int g = 1; g < KG; ++g)
+            v += *reinterpret_cast<const v4u*>(E0 + (g * S::WM * S::WN * 32 + sr) * EP + scol);
+          if (!part) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = __float_as_uint(__fmul_rn((float)(int32_t)v[r], sc));
+          }
+        }
         uint32_t* dst = out + row * a.N + col;
         if (a.vec && col + 3 < a.N) {
           *reinterpret_cast<v4u*>(dst) = v;
@@ -711,101 +520,195 @@ __global__ __launch_bounds__(kW8Threads, 1) void gemm_w8_kernel(GemmArgs a) {
   }
 }
 
-// Sums the split-K chunk sums in int64 and applies the scales.  A block owns
-// 64 consecutive outputs; its four waves add every fourth chunk (coalesced
-// 256-byte reads), then combine through LDS in a fixed order.
-template <int AC, int NS, bool BSIGNED>
-__global__ __launch_bounds__(256) void splitk_reduce_kernel(const int32_t* __restrict__ partial,
-                                                            int splits, int64_t MN,
-                                                            const float* alpha, const float* bscale,
-                                                            float* __restrict__ C) {
-  __shared__ int64_t part[4][64];
+// Sums the split-K chunk sums in int64 in a fixed order and applies the
+// scales.  A block's 16 waves work on 16 / P runs of 256 outputs, P waves on
+// each: a lane adds every P-th chunk of four outputs (16-byte loads, eight in
+// flight), and with P > 1 the P partial sums meet in LDS.  Few waves per run
+// where there are many outputs, all of them where there are few (reduce_waves).
+constexpr int kReduceThreads = 1024;
+
+template <int P, typename Scale>
+__global__ __launch_bounds__(kReduceThreads) void split_reduce_kernel(const int32_t* __restrict__ partial,
+                                                                     int splits, int64_t MN, int vec, Scale scale,
+                                                                     float* __restrict__ out) {
+  constexpr int RUNS = kReduceThreads / 64 / P;
+  __shared__ int64_t red[P > 1 ? kReduceThreads / 64 : 1][P > 1 ? 256 : 1];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t i = (int64_t)blockIdx.x * 64 + lane;
-  int64_t s = 0;
-  if (i < MN) {
-    int p = wave;
-    for (; p + 12 < splits; p += 16) {
-      const int32_t v0 = partial[(int64_t)p * MN + i], v1 = partial[(int64_t)(p + 4) * MN + i];
-      const int32_t v2 = partial[(int64_t)(p + 8) * MN + i], v3 = partial[(int64_t)(p + 12) * MN + i];
-      s += (int64_t)v0 + v1 + v2 + v3;
+  const int run = wave / P, part = wave % P;
+  const int64_t i0 = ((int64_t)blockIdx.x * RUNS + run) * 256 + 4 * lane;
+  int64_t s[4] = {0, 0, 0, 0};
+  if (vec && i0 + 3 < MN) {
+    for (int p0 = part; p0 < splits; p0 += 8 * P) {
+      v4i v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int p = p0 + P * u;
+        v[u] = p < splits ? *reinterpret_cast<const v4i*>(partial + (int64_t)p * MN + i0) : v4i{0, 0, 0, 0};
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) s[k] += v[u][k];
     }
-    for (; p < splits; p += 4) s += partial[(int64_t)p * MN + i];
+  } else {
+    for (int p = part; p < splits; p += P)
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (i0 + k < MN) s[k] += partial[(int64_t)p * MN + i0 + k];
   }
-  part[wave][lane] = s;
-  __syncthreads();
-  if (wave == 0 && i < MN) {
-    const int64_t tot = part[0][lane] + part[1][lane] + part[2][lane] + part[3][lane];
-    const float sc = epilogue_scale<AC, NS, BSIGNED>(*alpha, *bscale);
-    C[i] = __fmul_rn((float)tot, sc);
+  const float sc = scale();
+  if constexpr (P == 1) {
+    if (vec && i0 + 3 < MN) {
+      v4u v;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] = __float_as_uint(__fmul_rn((float)s[k], sc));
+      *reinterpret_cast<v4u*>(out + i0) = v;
+    } else {
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (i0 + k < MN) out[i0 + k] = __fmul_rn((float)s[k], sc);
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) red[wave][4 * lane + k] = s[k];
+    __syncthreads();
+    for (int t = threadIdx.x; t < RUNS * 256; t += kReduceThreads) {
+      const int r = t >> 8;
+      const int64_t i = ((int64_t)blockIdx.x * RUNS + r) * 256 + (t & 255);
+      int64_t tot = 0;
+#pragma unroll
+      for (int w = 0; w < P; ++w) tot += red[r * P + w][t & 255];
+      if (i < MN) out[i] = __fmul_rn((float)tot, sc);
+    }
   }
 }
 
+// out = scale * sum of `splits` chunk sums of MN outputs.  One wave per run of
+// 256 outputs when that already gives eight waves per CU (2^19 outputs) or
+// there are at most four chunks to add; 16 waves when there are few outputs.
+template <typename Scale>
+static void launch_split_reduce(const int32_t* partial, int splits, int64_t MN, Scale scale, float* out,
+                                hipStream_t st) {
+  const int vec = MN % 4 == 0 && ((uintptr_t)out & 15) == 0;
+  auto blocks = [&](int runs) { return dim3((unsigned)((MN + 256 * runs - 1) / (256 * runs))); };
+  if (MN >= (1 << 19) || splits <= 4)
+    hipLaunchKernelGGL((split_reduce_kernel<1, Scale>), blocks(16), dim3(kReduceThreads), 0, st, partial, splits, MN,
+                       vec, scale, out);
+  else if (MN >= (1 << 17) || splits <= 16)
+    hipLaunchKernelGGL((split_reduce_kernel<4, Scale>), blocks(4), dim3(kReduceThreads), 0, st, partial, splits, MN,
+                       vec, scale, out);
+  else
+    hipLaunchKernelGGL((split_reduce_kernel<16, Scale>), blocks(1), dim3(kReduceThreads), 0, st, partial, splits, MN,
+                       vec, scale, out);
+}
+
+template <int AC, int NS, bool BSIGNED>
+struct EpilogueScale {
+  const float* alpha;
+  const float* bscale;
+  __device__ __forceinline__ float operator()() const { return epilogue_scale<AC, NS, BSIGNED>(*alpha, *bscale); }
+};
+
 // ---- planning and launch ----------------------------------------------------------
 
+enum GemmTile {
+  kTile256x256, kTile128x256, kTile128x128, kTile64x128, kTile64x64, kTile32x64, kTile32x32, kTile64x64k1,
+  kGemmTiles
+};
+
+// A tile's shape and its cost in microseconds.  With S = k per workgroup / 128
+// stages, a workgroup alone on its CU takes S * stage1 + fixed1 (latency:
+// loads, barriers, epilogue), and a CU with several of them S * stage + fixed
+// each (throughput: expansion, LDS, MFMA, output stores).
+struct TileCost {
+  int lm, ln, lk;   // log2 of the tile's rows, columns and stage depth
+  float stage1, fixed1, stage, fixed;
+};
+
+// Least-squares fit to 1260 timings on an MI355X: 60 shapes (M and N from 1 to
+// 200704, K from 64 to 200704; LUQ, SMP sums and INT4 as the A operand), every
+// tile that covers them sensibly and 1 to 85 splits; the median deviation is 7%, and the
+// configuration with the least predicted time was within 1% (geometric mean) of
+// the best one measured, 17% at worst.  The former rule (256x256 tiles from 256
+// of them on, else 128x128 from 128 on, else 64x64, each with enough splits for
+// 512 workgroups) lost up to half on the shapes between: dX of 2048 x 1024 over K
+// = 4096 took 30.2 us as 128 tiles in four splits and takes 12.7 us as 256 tiles of
+// 64x128, because a split writes and reads back 4 bytes per output and chunk.
+constexpr TileCost kTileCost[kGemmTiles] = {
+    {8, 8, 7, 1.406f, 1.237f, 1.366f, 7.963f},  //
+    {7, 8, 7, 0.492f, 1.230f, 0.877f, 4.008f},  //
+    {7, 7, 7, 0.368f, 0.849f, 0.547f, 1.755f},  //
+    {6, 7, 8, 0.163f, 1.510f, 0.247f, 1.456f},   //
+    {6, 6, 9, 0.202f, 0.336f, 0.165f, 1.334f},    //
+    {5, 6, 9, 0.121f, 0.395f, 0.101f, 0.874f},    //
+    {5, 5, 10, 0.066f, 1.111f, 0.083f, 0.804f},   //
+    {6, 6, 7, 0.388f, 0.399f, 0.219f, 0.777f},
+};
+constexpr float kSplitCost = 3.4f;          // the reduction's launch
+constexpr float kSplitCostPerMOut = 1.12f;  // per 10^6 chunk sums written and read back
+constexpr int kCus = 256;
+
 struct GemmPlan {
-  int bm, bn, bk;
+  GemmTile tile;
   int64_t tiles_m, tiles_n;
   int splits;
   int64_t k_chunk;
 };
 
+// The tile and the number of splits with the least predicted time.  A split's k
+// range is a multiple of the tile's stage depth; min_splits keeps a chunk's int32
+// sums exact.
 static GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int64_t max_exact_k) {
-  GemmPlan p;
-  auto tiles = [&](int bm, int bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
-  // 256x256 tiles (the eight-wave kernel, one workgroup per CU) halve the
-  // expansion and LDS work per MAC; they pay off for long reductions.  Short
-  // reductions (the conv dX with K = 64) are bound by the fp32 output and
-  // prefer the 128x128 tile, which keeps two workgroups per CU.
-  if (K >= 1024 && tiles(256, 256) >= 256) {
-    p.bm = 256;
-    p.bn = 256;
-  } else if (M <= 64 && N >= 192 && K >= 65536) {
-    // few output rows and a long reduction (the conv dW: 64 x 576 x 200704):
-    // wide tiles so that the A rows are re-read for fewer column tiles
-    p.bm = 64;
-    p.bn = 192;
-  } else if (tiles(128, 128) >= 128) {
-    p.bm = 128;
-    p.bn = 128;
-  } else {
-    p.bm = 64;
-    p.bn = 64;
+  GemmPlan best{};
+  float best_cost = 0.0f;
+  const int64_t min_splits = K <= max_exact_k ? 1 : (K + max_exact_k - 1) / max_exact_k;
+  for (int t = 0; t < kGemmTiles; ++t) {
+    const TileCost& c = kTileCost[t];
+    auto ceil_shift = [](int64_t v, int l) { return (v + ((int64_t)1 << l) - 1) >> l; };
+    const int64_t tiles_m = ceil_shift(M, c.lm), tiles_n = ceil_shift(N, c.ln), nt = tiles_m * tiles_n;
+    const int64_t stages = ceil_shift(K, c.lk);
+    auto consider = [&](int64_t want) {
+      if (want < min_splits) want = min_splits;
+      if (want > stages) want = stages;
+      const int64_t chunk = want == 1 ? stages : (stages + want - 1) / want;
+      const int64_t splits = want == 1 ? 1 : (stages + chunk - 1) / chunk;
+      const float s = (float)(chunk << c.lk) * (1.0f / 128);
+      const int64_t nb = nt * splits;
+      // workgroups per CU: between the mean and the busiest CU's
+      const float mean = nb < kCus ? 1.0f : (float)nb * (1.0f / kCus);
+      const float per_cu = 0.5f * (mean + (float)((nb + kCus - 1) / kCus));
+      const float alone = s * c.stage1 + c.fixed1, shared = per_cu * (s * c.stage + c.fixed);
+      float cost = alone > shared ? alone : shared;
+      if (splits > 1) cost += kSplitCost + kSplitCostPerMOut * 1e-6f * (float)(M * N) * (float)splits;
+      if (best.splits == 0 || cost < best_cost) {
+        best_cost = cost;
+        best = GemmPlan{(GemmTile)t, tiles_m, tiles_n, (int)splits, chunk << c.lk};
+      }
+    };
+    consider(1);
+    // splits only where the tiles leave CUs idle (up to two workgroups per CU)
+    // and the reduction's launch does not cost more than there is to gain
+    if (nt < kCus && stages > 1 && best_cost > kSplitCost + c.fixed1) {
+      for (int64_t s = 2; s * nt < 2 * kCus && s <= stages; s *= 2) consider(s);
+      consider(kCus / nt);
+    }
   }
-  // a reduction of at most 64 fits one 64-deep stage: half the LDS, so more
-  // workgroups per CU overlap their loads with other tiles' output stores
-  p.bk = (K <= 64 && p.bm == 128) ? 64 : 128;
-  p.tiles_m = (M + p.bm - 1) / p.bm;
-  p.tiles_n = (N + p.bn - 1) / p.bn;
-  const int64_t nt = p.tiles_m * p.tiles_n;
-  const int64_t ktiles = (K + kKAlign - 1) / kKAlign;
-  int64_t splits = 1;
-  // too few tiles to fill 256 CUs: split the reduction (>= 8 k-stages each);
-  // the wide tiles aim at one workgroup per CU, since every split adds
-  // M x N partial sums to write and read back
-  if (nt < 256) {
-    const int64_t target = p.bn == 192 ? 256 : 512;
-    splits = (target + nt - 1) / nt;
-    const int64_t max_by_len = ktiles / 8 > 0 ? ktiles / 8 : 1;
-    if (splits > max_by_len) splits = max_by_len;
-  }
-  // int32-exact chunk length
-  const int64_t min_splits = (K + max_exact_k - 1) / max_exact_k;
-  if (splits < min_splits) splits = min_splits;
-  if (splits < 1) splits = 1;
-  const int64_t chunk_tiles = (ktiles + splits - 1) / splits;
-  p.k_chunk = chunk_tiles * kKAlign;
-  p.splits = (int)((ktiles + chunk_tiles - 1) / chunk_tiles);
-  return p;
+  return best;
 }
 
-template <int BM, int BN, int BK, int AC, int NS, bool BSIGNED>
+template <typename S, int AC, int NS, bool BSIGNED>
 static void launch_tile(const GemmArgs& a, dim3 grid, hipStream_t st) {
-  if (a.K % kKAlign == 0)
-    hipLaunchKernelGGL((gemm_luq_int4_kernel<BM, BN, BK, AC, NS, BSIGNED, true>), grid, dim3(kGemmThreads), 0, st, a);
+  // Prefetch depth by register budget (deeper modes spill where not taken): 256
+  // registers a wave for the 256x256 tile, 128 for most smaller ones, where one
+  // k-step ahead measured best.
+  constexpr bool kBig = S::BM == 256, kLuq1 = AC == kAcLuq && NS == 1, kLuq2 = AC == kAcLuq && NS == 2;
+  constexpr int kSmall = S::BM == 64 && S::BN == 128 ? 1 : 2;
+  constexpr int kPfFull = !kBig ? kSmall : kLuq2 ? 2 : AC == kAcSum2 && !BSIGNED ? 2 : 3;
+  constexpr int kPfPart = !kBig ? kSmall : kLuq1 ? 2 : kLuq2 ? 0 : 1;
+  if (a.K % S::BK == 0)
+    hipLaunchKernelGGL((gemm_tile_kernel<AC, NS, BSIGNED, true, kPfFull, S>), grid, dim3(S::THREADS), 0, st, a);
   else
-    hipLaunchKernelGGL((gemm_luq_int4_kernel<BM, BN, BK, AC, NS, BSIGNED, false>), grid, dim3(kGemmThreads), 0, st,
-                       a);
+    hipLaunchKernelGGL((gemm_tile_kernel<AC, NS, BSIGNED, false, kPfPart, S>), grid, dim3(S::THREADS), 0, st, a);
 }
 
 template <int AC, int NS, bool BSIGNED>
@@ -817,29 +720,18 @@ static hipError_t gemm_launch_t(const GemmArgs& a0, const GemmPlan& p, hipStream
   const dim3 grid((unsigned)(p.tiles_m * p.tiles_n), (unsigned)p.splits);
   // 16-byte stores need 16-byte aligned rows
   a.vec = (a.N % 4) == 0 && (((uintptr_t)(a.partial ? (void*)a.partial : (void*)a.C)) & 15) == 0;
-  if (p.bm == 256) {
-    // prefetch depth by register budget (deeper modes spill where not taken)
-    constexpr bool kLuq1 = AC == kAcLuq && NS == 1;
-    constexpr int kPfFull = AC == kAcSum2 ? (BSIGNED ? 3 : 2) : kLuq1 ? 2 : 1;
-    constexpr int kPfPart = AC == kAcSum2 || kLuq1 ? 2 : AC == kAcLuq ? 0 : 1;
-    if (a.K % kKAlign == 0)
-      hipLaunchKernelGGL((gemm_w8_kernel<AC, NS, BSIGNED, true, kPfFull>), grid, dim3(kW8Threads), 0, st, a);
-    else
-      hipLaunchKernelGGL((gemm_w8_kernel<AC, NS, BSIGNED, false, kPfPart>), grid, dim3(kW8Threads), 0, st, a);
+  switch (p.tile) {
+    case kTile256x256: launch_tile<Tile256x256, AC, NS, BSIGNED>(a, grid, st); break;
+    case kTile128x256: launch_tile<Tile128x256, AC, NS, BSIGNED>(a, grid, st); break;
+    case kTile128x128: launch_tile<Tile128x128, AC, NS, BSIGNED>(a, grid, st); break;
+    case kTile64x128: launch_tile<Tile64x128, AC, NS, BSIGNED>(a, grid, st); break;
+    case kTile64x64: launch_tile<Tile64x64, AC, NS, BSIGNED>(a, grid, st); break;
+    case kTile32x64: launch_tile<Tile32x64, AC, NS, BSIGNED>(a, grid, st); break;
+    case kTile32x32: launch_tile<Tile32x32, AC, NS, BSIGNED>(a, grid, st); break;
+    default: launch_tile<Tile64x64k1, AC, NS, BSIGNED>(a, grid, st); break;
   }
-  else if (p.bm == 128 && p.bk == 64)
-    launch_tile<128, 128, 64, AC, NS, BSIGNED>(a, grid, st);
-  else if (p.bm == 128)
-    launch_tile<128, 128, 128, AC, NS, BSIGNED>(a, grid, st);
-  else if (p.bn == 192)
-    launch_tile<64, 192, 128, AC, NS, BSIGNED>(a, grid, st);
-  else
-    launch_tile<64, 64, 128, AC, NS, BSIGNED>(a, grid, st);
-  if (p.splits > 1) {
-    const int64_t MN = a.M * a.N;
-    hipLaunchKernelGGL((splitk_reduce_kernel<AC, NS, BSIGNED>), dim3((unsigned)((MN + 63) / 64)), dim3(256), 0, st,
-                       a.partial, p.splits, MN, a.alpha, a.bscale, a.C);
-  }
+  if (p.splits > 1)
+    launch_split_reduce(a.partial, p.splits, a.M * a.N, EpilogueScale<AC, NS, BSIGNED>{a.alpha, a.bscale}, a.C, st);
   return hipGetLastError();
 }
 

@@ -1,0 +1,71 @@
+"""GPU parity of every GEMM tile shape through the C ABI.
+
+The planner picks a tile and a number of splits by predicted time; the shapes
+below select each tile, with M and N at and just past tile edges, K a multiple
+of the tile's stage depth (whole stages) and not (the last stage partly past the
+end), one stage only, and split reductions whose last split is shorter.  Every A
+operand kind (LUQ, two planes, the int8 sums, INT4) runs on every shape.  Outputs
+are compared with the oracle within 1e-5 of sum |a b| and bit for bit with the
+fp32 epilogue applied to the exact integer sums.
+"""
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+from test_gpu_parity import _gemm_case, _wgrad_case, _fwd_case  # noqa: E402
+from test_gpu_smp_sum import _dgrad_sum_case  # noqa: E402
+
+
+@pytest.fixture(scope="module")
+def L():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2112_10769_amd as lib
+    return lib
+
+
+SHAPES = [
+    (4090, 4104, 2080),   # 256 x 256, half a stage left over
+    (4096, 2048, 1024),   # 128 x 256
+    (4099, 2056, 1120),   # 128 x 128
+    (2050, 1032, 544),    # 128 x 128, a quarter of a stage left over
+    (2048, 1024, 512),    # 64 x 128
+    (1060, 1032, 1056),   # 64 x 128, an eighth of a stage left over
+    (1024, 1024, 1024),   # 64 x 64, four k-groups
+    (200, 264, 1056),     # 32 x 64
+    (1, 64, 512),         # one row
+    (33, 200, 2080),      # 32 x 32, eight k-groups
+    (32, 64, 1024),       # 32 x 32, one stage
+    (520, 520, 96),       # 64 x 64, one k-group, less than a stage
+    (130, 264, 16416),    # 32 x 64, nine splits
+    (40, 72, 40000),      # 32 x 32, forty splits, the last one short
+]
+
+
+@pytest.mark.parametrize("M,N,K", SHAPES)
+@pytest.mark.parametrize("signed", [True, False])
+def test_tile_luq(L, M, N, K, signed):
+    _gemm_case(L, M, N, K, 1, signed, seed=M + N + K)
+
+
+@pytest.mark.parametrize("M,N,K", SHAPES)
+def test_tile_two_planes(L, M, N, K):
+    _gemm_case(L, M, N, K, 2, True, seed=M + N + K + 1)
+
+
+@pytest.mark.parametrize("M,N,K", SHAPES)
+def test_tile_smp_sum(L, M, N, K):
+    _dgrad_sum_case(L, M, N, K, True, seed=M + N + K + 2)
+
+
+@pytest.mark.parametrize("M,N,K", SHAPES)
+@pytest.mark.parametrize("xsig", [True, False])
+def test_tile_fwd(L, M, N, K, xsig):
+    # an odd number of output columns: scalar stores
+    _fwd_case(L, M, N - 3, K, xsig, True, seed=M + N + K + 3)
+
+
+@pytest.mark.parametrize("T,Nout,Kin", [(1056, 1064, 520), (65568, 72, 40), (96, 1032, 264)])
+def test_tile_wgrad(L, T, Nout, Kin):
+    _wgrad_case(L, T, Nout, Kin, 1, signed=False, seed=T + Nout + Kin)
