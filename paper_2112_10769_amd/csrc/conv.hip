@@ -623,7 +623,7 @@ hipError_t launch_conv3x3_dgrad(const uint8_t* g, int64_t g_plane, int ns, const
 // halves of the workgroup's pixel range, each with its own double-buffered
 // stages; their sums are added through LDS at the end.  The reduction over
 // pixel ranges is split over workgroups, and their int32 sums are combined
-// exactly, in a fixed order, by conv_wgrad_reduce_kernel.
+// exactly, in a fixed order, by split_reduce_kernel.
 //
 // Bytes in LDS are in natural pixel order (the shifts need it).  Carriers are
 // those of the GEMMs: LUQ codes as their values (two samples as their int8
@@ -983,53 +983,6 @@ __global__ __launch_bounds__(kWgThreads, 1) void conv3x3_wgrad_kernel(ConvWgArgs
   }
 }
 
-// dW = scale * (sum over splits of the int32 sums), summed exactly in int64
-// in a fixed order.  A block owns 256 consecutive outputs; its 16 waves take
-// the splits p = wave, wave + 16, ... with 16-byte loads (4 outputs a lane,
-// several splits in flight), then the 16 partial sums are added through LDS.
-constexpr int kRedThreads = 1024;
-
-template <int NS, bool ASIGNED>
-__global__ __launch_bounds__(kRedThreads) void conv_wgrad_reduce_kernel(const int32_t* __restrict__ partial,
-                                                                       int splits, int64_t MN, int vec,
-                                                                       const float* alpha, const float* ascale,
-                                                                       float* __restrict__ out) {
-  __shared__ int64_t red[kRedThreads / 64][256];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t i0 = (int64_t)blockIdx.x * 256 + 4 * lane;
-  int64_t s[4] = {0, 0, 0, 0};
-  if (vec && i0 + 3 < MN) {
-    // up to 8 splits per wave in flight before the first add
-    for (int p0 = wave; p0 < splits; p0 += 8 * 16) {
-      v4i v[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int p = p0 + 16 * u;
-        v[u] = p < splits ? *reinterpret_cast<const v4i*>(partial + (int64_t)p * MN + i0) : v4i{0, 0, 0, 0};
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u)
-#pragma unroll
-        for (int k = 0; k < 4; ++k) s[k] += v[u][k];
-    }
-  } else {
-    for (int p = wave; p < splits; p += 16)
-#pragma unroll
-      for (int k = 0; k < 4; ++k)
-        if (i0 + k < MN) s[k] += partial[(int64_t)p * MN + i0 + k];
-  }
-#pragma unroll
-  for (int k = 0; k < 4; ++k) red[wave][4 * lane + k] = s[k];
-  __syncthreads();
-  if (threadIdx.x < 256) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    int64_t tot = 0;
-#pragma unroll
-    for (int w = 0; w < kRedThreads / 64; ++w) tot += red[w][threadIdx.x];
-    if (i < MN) out[i] = __fmul_rn((float)tot, epilogue_scale<kAcLuq, NS, ASIGNED>(*alpha, *ascale));
-  }
-}
-
 // ---------------------------------------------------------------------------
 // Weight gradient, row form (W <= 64, C and Cout multiples of 32).  A
 // workgroup owns one 32 x 32 (o, c) block of all nine taps over a range of
@@ -1054,7 +1007,7 @@ __global__ __launch_bounds__(kRedThreads) void conv_wgrad_reduce_kernel(const in
 // three MFMAs.  Both operands use the GEMMs' expansions, which share one k
 // permutation, so the products summed are the same.  The eight waves add
 // their tiles through LDS; the workgroup writes the int32 sums of its block
-// for its row range, and conv_wgrad_reduce_kernel adds the ranges in int64
+// for its row range, and split_reduce_kernel adds the ranges in int64
 // (with one range the scales are applied directly).
 // ---------------------------------------------------------------------------
 constexpr int kWrThreads = 512;
@@ -1091,7 +1044,16 @@ struct ConvWrArgs {
   int vec;               // 16-byte stores of dW rows
 };
 
-template <int NS, bool ASIGNED>
+// Rows per k-step (G): a lane half supplies 16 consecutive k of the 32-deep
+// MFMA, as two 8-code words, and which image row they come from is free.  A row
+// of more than 16 pixels fills one or two k-steps (G = 1).  Narrower rows would
+// leave most of a k-step empty (14 of 32 columns, 7 of 32), so the lane halves
+// (W <= 16, G = 2) or the four half-and-word slots (W <= 8, G = 4) walk runs of
+// rows of their own: row bounds, image rows and window offsets are then per
+// lane, a kernel row off the image is cleared in the gradient fragment instead
+// of skipped, and G rows share the nine MFMAs.  64 x 14 x 14, 256 -> 256: kernel
+// 24.0 -> 17.4 us; 64 x 7 x 7, 512 -> 512: 36.6 -> 18.7 us.
+template <int NS, bool ASIGNED, int G>
 __global__ __launch_bounds__(kWrThreads, 1) void conv3x3_wgrad_rows_kernel(ConvWrArgs a) {
   __shared__ __attribute__((aligned(16))) uint32_t lds[kWrLdsBytes / 4];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -1186,6 +1148,136 @@ __global__ __launch_bounds__(kWrThreads, 1) void conv3x3_wgrad_rows_kernel(ConvW
       __builtin_amdgcn_s_waitcnt(kWaitVm0);
     }
     __syncthreads();
+
+    if constexpr (G > 1) {
+      // ---- G runs of rows per wave: walker w = wave * G + slot, its run
+      // [r0, r0 + n) of the chunk.  Step i reads activation row r0 - 1 + i and,
+      // for i >= 2, multiplies gradient row r0 - 2 + i; every walker takes the
+      // longest run's steps, re-reading its last rows past its own end (the
+      // gradient is cleared there).
+      constexpr int D = G == 4 ? 2 : 1;     // walkers per lane (its two words)
+      constexpr int XW = G == 4 ? 3 : 4;    // dwords of an activation window
+      constexpr int GW = G == 4 ? 2 : 3;    // dwords of a gradient row
+      const int per = (nrow + kWrWaves * G - 1) / (kWrWaves * G) + 2;
+      int r0[D], n[D], y[D];
+#pragma unroll
+      for (int d = 0; d < D; ++d) {
+        const int w = wave * G + h * D + d;
+        r0[d] = cr0 + w * nrow / (kWrWaves * G);
+        n[d] = cr0 + (w + 1) * nrow / (kWrWaves * G) - r0[d];
+        y[d] = r0[d] % a.H;
+      }
+      const uint32_t* lg = ldsg + r32 * pg;
+      const uint32_t* la = ldsa + r32 * pa;
+      const int gplane = 4 * rg, ga = (int)a0, gg = (int)g0;
+      // valid codes of a row's first and second word
+      const uint32_t m0 = a.W >= 8 ? ~0u : (1u << (4 * a.W)) - 1u;
+      const uint32_t m1 = a.W >= 16 ? ~0u : a.W <= 8 ? 0u : (1u << (4 * (a.W - 8))) - 1u;
+      // column W - 1 with kw = 2
+      const uint32_t e0 = a.W <= 8 ? ~(0xFu << (4 * (a.W - 1))) : ~0u;
+      const uint32_t e1 = a.W > 8 ? ~(0xFu << (4 * (a.W - 9))) : ~0u;
+      // the three shifted activation fragments of step i: the window from column
+      // -1 on, aligned to it, then cut at kw = 0, 1, 2
+      auto expand_x = [&](v4i (&w)[3], int i) {
+        uint32_t x[3][2];
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+          const int c = (r0[d] - 1 + min(i, n[d] + 1)) * a.W - 1;   // code of column -1
+          const uint32_t* src = la + ((c >> 3) - ga);
+          const uint32_t sh = 4 * (c & 7);
+          uint32_t v[XW], q[XW - 1];
+#pragma unroll
+          for (int j = 0; j < XW; ++j) v[j] = src[j];
+#pragma unroll
+          for (int j = 0; j < XW - 1; ++j) q[j] = __builtin_amdgcn_alignbit(v[j + 1], v[j], sh);
+#pragma unroll
+          for (int j = 0; j < XW - 2; ++j) {
+            x[0][d + j] = q[j];
+            x[1][d + j] = __builtin_amdgcn_alignbit(q[j + 1], q[j], 4);
+            x[2][d + j] = __builtin_amdgcn_alignbit(q[j + 1], q[j], 8);
+          }
+        }
+        x[0][0] &= ~0xFu;
+        if constexpr (G == 4) x[0][1] &= ~0xFu;
+        x[2][0] &= e0;
+        x[2][1] &= G == 4 ? e0 : e1;
+#pragma unroll
+        for (int kw = 0; kw < 3; ++kw) {
+          uint32_t l0, h0, l1, h1;
+          expand_int4<ASIGNED>(x[kw][0], l0, h0);
+          expand_int4<ASIGNED>(x[kw][1], l1, h1);
+          w[kw] = v4i{(int)l0, (int)h0, (int)l1, (int)h1};
+        }
+      };
+      // the gradient fragments of step i (row r0 - 2 + i): for the middle kernel
+      // row, and cleared where the upper or the lower one leaves the image
+      auto expand_g = [&](v4i (&f)[3], int i) {
+        uint32_t x[NS][2];
+        bool top[D], bot[D];
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+          const int k = i - 2;
+          const int c = (r0[d] + min(k, max(n[d] - 1, 0))) * a.W;
+          const uint32_t* src = lg + ((c >> 3) - gg);
+          const uint32_t sh = 4 * (c & 7), live = k < n[d] ? ~0u : 0u;
+#pragma unroll
+          for (int p = 0; p < NS; ++p) {
+            uint32_t v[GW];
+#pragma unroll
+            for (int j = 0; j < GW; ++j) v[j] = src[p * gplane + j];
+#pragma unroll
+            for (int j = 0; j < GW - 1; ++j)
+              x[p][d + j] = __builtin_amdgcn_alignbit(v[j + 1], v[j], sh) & (G == 4 || j == 0 ? m0 : m1) & live;
+          }
+          top[d] = y[d] > 0;
+          bot[d] = y[d] < a.H - 1;
+          y[d] = y[d] + 1 == a.H ? 0 : y[d] + 1;
+        }
+        uint32_t w[4];
+        if constexpr (NS == 1) {
+          expand_luq(x[0][0], w[0], w[1]);
+          expand_luq(x[0][1], w[2], w[3]);
+        } else {
+#pragma unroll
+          for (int d = 0; d < 2; ++d) {
+            uint32_t l0, h0, l1, h1;
+            expand_luq_excess64(x[0][d], l0, h0);
+            expand_luq_excess64(x[1][d], l1, h1);
+            w[2 * d] = (l0 + l1) ^ 0x80808080u;
+            w[2 * d + 1] = (h0 + h1) ^ 0x80808080u;
+          }
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int d = G == 4 ? j >> 1 : 0;
+          f[0][j] = top[d] ? (int)w[j] : 0;
+          f[1][j] = (int)w[j];
+          f[2][j] = bot[d] ? (int)w[j] : 0;
+        }
+      };
+      auto step = [&](int i, v4i (&wj)[3], const v4i (&w0)[3], const v4i (&w1)[3]) {
+        if (i >= per) return;
+        expand_x(wj, i);
+        if (i < 2) return;
+        v4i f[3];
+        expand_g(f, i);
+#pragma unroll
+        for (int kw = 0; kw < 3; ++kw) acc[kw] = __builtin_amdgcn_mfma_i32_32x32x32_i8(w0[kw], f[0], acc[kw], 0, 0, 0);
+#pragma unroll
+        for (int kw = 0; kw < 3; ++kw)
+          acc[3 + kw] = __builtin_amdgcn_mfma_i32_32x32x32_i8(w1[kw], f[1], acc[3 + kw], 0, 0, 0);
+#pragma unroll
+        for (int kw = 0; kw < 3; ++kw)
+          acc[6 + kw] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wj[kw], f[2], acc[6 + kw], 0, 0, 0);
+      };
+      v4i win[3][3];
+      for (int i = 0; i < per; i += 3) {
+        step(i, win[0], win[1], win[2]);
+        step(i + 1, win[1], win[2], win[0]);
+        step(i + 2, win[2], win[0], win[1]);
+      }
+      continue;
+    }
 
     // ---- this wave's rows of the chunk, one pass per k-step: step i reads
     // activation row r0 - 1 + i and, for i >= 2, multiplies gradient row
@@ -1419,22 +1511,23 @@ int64_t conv3x3_wgrad_blocks(int64_t T, int64_t C, int64_t Cout) {
 template <int NS, bool ASIGNED>
 static void conv_wgrad_launch_t(const ConvWgArgs& a, unsigned blocks, hipStream_t st) {
   hipLaunchKernelGGL((conv3x3_wgrad_kernel<NS, ASIGNED>), dim3(blocks), dim3(kWgThreads), 0, st, a);
-  if (a.partial) {
-    const int64_t MN = (int64_t)a.Cout * 9 * a.C;
-    const int vec = (MN % 4) == 0;
-    hipLaunchKernelGGL((conv_wgrad_reduce_kernel<NS, ASIGNED>), dim3((unsigned)((MN + 255) / 256)),
-                       dim3(kRedThreads), 0, st, a.partial, a.nsplit, MN, vec, a.alpha, a.ascale, a.dw);
-  }
+  if (a.partial)
+    launch_split_reduce(a.partial, a.nsplit, (int64_t)a.Cout * 9 * a.C,
+                        EpilogueScale<kAcLuq, NS, ASIGNED>{a.alpha, a.ascale}, a.dw, st);
 }
 
 template <int NS, bool ASIGNED>
 static void conv_wr_launch_t(const ConvWrArgs& a, unsigned blocks, hipStream_t st) {
-  hipLaunchKernelGGL((conv3x3_wgrad_rows_kernel<NS, ASIGNED>), dim3(blocks), dim3(kWrThreads), 0, st, a);
-  if (a.partial) {
-    const int64_t MN = (int64_t)a.Cout * 9 * a.C;
-    hipLaunchKernelGGL((conv_wgrad_reduce_kernel<NS, ASIGNED>), dim3((unsigned)((MN + 255) / 256)),
-                       dim3(kRedThreads), 0, st, a.partial, a.nr, MN, 1, a.alpha, a.ascale, a.dw);
-  }
+  // rows that share a k-step: as many as fit its columns
+  if (a.W <= 8)
+    hipLaunchKernelGGL((conv3x3_wgrad_rows_kernel<NS, ASIGNED, 4>), dim3(blocks), dim3(kWrThreads), 0, st, a);
+  else if (a.W <= 16)
+    hipLaunchKernelGGL((conv3x3_wgrad_rows_kernel<NS, ASIGNED, 2>), dim3(blocks), dim3(kWrThreads), 0, st, a);
+  else
+    hipLaunchKernelGGL((conv3x3_wgrad_rows_kernel<NS, ASIGNED, 1>), dim3(blocks), dim3(kWrThreads), 0, st, a);
+  if (a.partial)
+    launch_split_reduce(a.partial, a.nr, (int64_t)a.Cout * 9 * a.C,
+                        EpilogueScale<kAcLuq, NS, ASIGNED>{a.alpha, a.ascale}, a.dw, st);
 }
 
 hipError_t launch_conv3x3_wgrad(const uint8_t* g, int64_t g_plane, int ns, const float* alpha, const uint8_t* act,

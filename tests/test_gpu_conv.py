@@ -224,6 +224,26 @@ def test_conv_wgrad_parity(L, B, H, W, C, Cout, ns):
     _wgrad_case(L, B, H, W, C, Cout, ns=ns, seed=B * 1000 + H * 100 + W + C + Cout)
 
 
+@pytest.mark.parametrize("B,H,W,C,Cout", [
+    (32, 7, 7, 64, 32),       # four rows per k-step, every row at another nibble offset
+    (4, 8, 8, 32, 64),        # a full word per row; fewer rows than walkers in some waves
+    (32, 1, 1, 32, 32),       # height and width 1: every tap but the middle one off the image
+    (16, 2, 3, 32, 32),       # height 2: both outer kernel rows off for every row
+    (1, 32, 5, 32, 32),       # one image, walkers with no rows
+    (8, 100, 7, 512, 512),    # one range of 800 rows staged in two chunks
+    (32, 14, 14, 64, 96),     # two rows per k-step
+    (32, 9, 9, 32, 32),       # width 9: one code in the second word
+    (2, 16, 15, 32, 32),      # width 15, the right edge column in the second word
+    (4, 4, 16, 32, 32),       # width 16: no padding columns
+    (32, 1, 11, 32, 64),      # height 1
+])
+@pytest.mark.parametrize("ns,asig", [(1, False), (1, True), (2, False)])
+def test_conv_wgrad_narrow_rows(L, B, H, W, C, Cout, ns, asig):
+    """Images of at most 16 pixels: several rows share a k-step, each lane half
+    (or each 8-code word of one) walking rows of its own."""
+    _wgrad_case(L, B, H, W, C, Cout, ns=ns, asig=asig, seed=B * 100 + H * 10 + W + C)
+
+
 @pytest.mark.parametrize("R,ns", [(6, 1), (5, 2)])
 @pytest.mark.parametrize("B,H,W,C,Cout", [(4, 14, 16, 64, 64), (16, 28, 28, 64, 64)])
 def test_conv_wgrad_parity_wide_levels(L, B, H, W, C, Cout, R, ns):
