@@ -302,6 +302,265 @@ static void conv_launch_w(const ConvArgs& a, int wsigned, dim3 grid, hipStream_t
 }
 
 // ---------------------------------------------------------------------------
+// Activation gradient, deep form (more than 64 output channels, images of at most
+// 62 pixels, at most one workgroup per CU): the tile form with its long reduction
+// spread over eight waves.  A workgroup owns 128 pixels x 64 channels; its waves are
+// four k-groups of two pixel groups, a wave 64 pixels x 64 channels (2 x 2 MFMA
+// tiles) of one of the four 32-deep k-steps of each chunk of 128 output channels, and
+// the k-groups' sums meet in LDS at the end.  Per chunk the gradient codes of the
+// tile and its halo are expanded into LDS and the 9 x 64 weight rows stored there as
+// they are: a wave expands its own two fragments of a tap (12 VALU) for four MFMAs.
+// Both are double-buffered with one barrier per chunk, the next chunk's pieces stored
+// between the taps, and the codes of the two chunks after it are in registers or on
+// their way: every workgroup reaches a chunk of the weights at the same time, so its
+// first use comes from beyond L2.
+// The tile form leaves deep layers at one wave per SIMD on part of the chip (64 x 7
+// x 7: 104 workgroups of four waves) and expands 37 KB of weights per 64 channels.
+// 64 x 7 x 7, 512 -> 512: 26.2 -> 14.6 us; 32 x 14 x 14, 256 -> 256: 16.5 -> 11.9 us;
+// a fixed part of about 8 us (cold operands, epilogue) is what remains of it.
+// ---------------------------------------------------------------------------
+constexpr int kDdThreads = 512;
+constexpr int kDdMaxW = 62;      // 2 gradient pieces per thread and chunk
+
+constexpr int kDdBM = 128;
+
+struct ConvDd {
+  static constexpr int PX = kDdBM / 64, KG = 8 / PX;        // pixel groups, k-groups
+  static constexpr int CK = 32 * KG;                        // output channels per chunk
+  static constexpr int kPitch = CK + 16;                    // expanded codes of a pixel
+  static constexpr int kHalo = kDdBM + 2 * (kDdMaxW + 1);
+  static constexpr int kABytes = kHalo * kPitch;            // one buffer of expanded codes
+  static constexpr int kBBytes = 9 * kConvBN * 16 * KG;     // one buffer of weight codes
+  static constexpr int kZero = kABytes + kBBytes;           // then an all-zero row
+  static constexpr int kBuf = kZero + kPitch;
+  static constexpr int kAPieces = (KG * kHalo + kDdThreads - 1) / kDdThreads;
+  static constexpr int kBPieces = (KG * 9 * kConvBN + kDdThreads - 1) / kDdThreads;
+  // slot of 16-byte part `part` of weight row r: permuted so that the equal parts
+  // of sixteen rows cover all banks
+  static __device__ __forceinline__ int slot(int r, int part) { return part ^ ((r >> 2) & (KG - 1)); }
+};
+
+template <int NS, bool WSIGNED>
+__global__ __launch_bounds__(kDdThreads, 2) void conv3x3_dgrad_deep_kernel(ConvArgs a) {
+  using D = ConvDd;
+  constexpr int KG = D::KG, PX = D::PX;
+  __shared__ __attribute__((aligned(16))) uint8_t lds[2 * D::kBuf];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int kg = wave / PX, wp = wave % PX, h = lane >> 5;
+  // tiles pixel-major, the channel tiles of one pixel tile together; each XCD
+  // (blocks are dealt round-robin over the 8) takes a run of them
+  const int ctiles = (a.C + kConvBN - 1) / kConvBN, total = a.tiles_m * ctiles;
+  const int xcd = blockIdx.x & 7, q8 = total >> 3, r8 = total & 7;
+  const int L = xcd * q8 + min(xcd, r8) + (blockIdx.x >> 3);
+  const int t0 = (L / ctiles) * kDdBM, c0 = (L % ctiles) * kConvBN;
+  const int hoff = a.W + 1, hrows = kDdBM + 2 * hoff;
+  const int rowb = a.Cout >> 1;
+  const int nchunks = (a.Cout + D::CK - 1) / D::CK;
+
+  __amdgpu_buffer_rsrc_t rsg[NS];
+#pragma unroll
+  for (int s = 0; s < NS; ++s)
+    rsg[s] = __builtin_amdgcn_make_buffer_rsrc((void*)(a.g + s * a.g_plane), (short)0, a.T * rowb, kBufferFlags);
+  const __amdgpu_buffer_rsrc_t rsw =
+      __builtin_amdgcn_make_buffer_rsrc((void*)a.w, (short)0, 9 * a.C * rowb, kBufferFlags);
+  for (int i = tid; i < 2 * D::kPitch / 16; i += kDdThreads) {
+    const int b = i >= D::kPitch / 16, j = i - b * (D::kPitch / 16);
+    reinterpret_cast<uint4*>(lds + b * D::kBuf + D::kZero)[j] = make_uint4(0, 0, 0, 0);
+  }
+
+  // pieces of 16 code bytes (32 of o): gradient pixel p / KG, weight row p / KG
+  // (tap * 64 + c), part p % KG of the chunk.  Offsets for chunk 0, advanced by CK / 2
+  // bytes a chunk; a part past Cout reads as zeros
+  const int part = tid % KG;
+  int offg[D::kAPieces], offw[D::kBPieces];
+#pragma unroll
+  for (int q = 0; q < D::kAPieces; ++q) {
+    const int p = (tid + q * kDdThreads) / KG, pix = t0 - hoff + p;
+    offg[q] = p < hrows && pix >= 0 && pix < a.T ? pix * rowb + part * 16 : kOutOfRange;
+  }
+#pragma unroll
+  for (int q = 0; q < D::kBPieces; ++q) {
+    const int row = (tid + q * kDdThreads) / KG, c = c0 + (row & 63);
+    offw[q] = row < 9 * kConvBN && c < a.C ? ((row >> 6) * a.C + c) * rowb + part * 16 : kOutOfRange;
+  }
+  struct Regs {
+    v4u g[D::kAPieces][NS];
+    v4u w[D::kBPieces];
+  };
+  auto load_w = [&](Regs& r, int cc, int q) __attribute__((always_inline)) {
+    const bool in = cc * D::CK + part * 32 < a.Cout;
+    const int off = in && offw[q] != kOutOfRange ? offw[q] + cc * (D::CK / 2) : kOutOfRange;
+    r.w[q] = __builtin_amdgcn_raw_buffer_load_b128(rsw, off, 0, 0);
+  };
+  auto load_g = [&](Regs& r, int cc, int q) __attribute__((always_inline)) {
+    const bool in = cc * D::CK + part * 32 < a.Cout;
+    const int off = in && offg[q] != kOutOfRange ? offg[q] + cc * (D::CK / 2) : kOutOfRange;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) r.g[q][s] = __builtin_amdgcn_raw_buffer_load_b128(rsg[s], off, 0, 0);
+  };
+  auto load = [&](Regs& r, int cc) __attribute__((always_inline)) {
+#pragma unroll
+    for (int q = 0; q < D::kBPieces; ++q) load_w(r, cc, q);
+#pragma unroll
+    for (int q = 0; q < D::kAPieces; ++q) load_g(r, cc, q);
+  };
+  auto store_w = [&](const Regs& r, int buf, int q) __attribute__((always_inline)) {
+    const int row = (tid + q * kDdThreads) / KG;
+    if (row < 9 * kConvBN)
+      *reinterpret_cast<v4u*>(lds + buf * D::kBuf + D::kABytes + (row * KG + D::slot(row, part)) * 16) = r.w[q];
+  };
+  auto store_g = [&](const Regs& r, int buf, int q) __attribute__((always_inline)) {
+    const int p = (tid + q * kDdThreads) / KG;
+    if (p < D::kHalo) {
+      uint32_t w[8];
+#pragma unroll
+      for (int d = 0; d < 4; ++d) {
+        if constexpr (NS == 1) {
+          expand_luq(r.g[q][0][d], w[2 * d], w[2 * d + 1]);
+        } else {
+          uint32_t l0, h0, l1, h1;
+          expand_luq_excess64(r.g[q][0][d], l0, h0);
+          expand_luq_excess64(r.g[q][1][d], l1, h1);
+          w[2 * d] = (l0 + l1) ^ 0x80808080u;
+          w[2 * d + 1] = (h0 + h1) ^ 0x80808080u;
+        }
+      }
+      uint4* dst = reinterpret_cast<uint4*>(lds + buf * D::kBuf + p * D::kPitch + part * 32);
+      dst[0] = make_uint4(w[0], w[1], w[2], w[3]);
+      dst[1] = make_uint4(w[4], w[5], w[6], w[7]);
+    }
+  };
+
+  Regs r0, r1;
+  load(r0, 0);
+  load(r1, 1);
+  // per lane and tap: the LDS bytes of its A-fragment rows in a buffer, the zero
+  // row where the tap leaves the image
+  int atap[9][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int rr = wp * 64 + i * 32 + (lane & 31), t = t0 + rr;
+    const int row = t / a.W, x = t - row * a.W, y = row % a.H;
+#pragma unroll
+    for (int kh = 0; kh < 3; ++kh)
+#pragma unroll
+      for (int kw = 0; kw < 3; ++kw) {
+        const int ys = y + 1 - kh, xs = x + 1 - kw;
+        const bool ok = t < a.T && ys >= 0 && ys < a.H && xs >= 0 && xs < a.W;
+        atap[kh * 3 + kw][i] =
+            (ok ? (rr + hoff + (1 - kh) * a.W + (1 - kw)) * D::kPitch + kg * 32 : D::kZero) + h * 16;
+      }
+  }
+  // weight rows l%32 and 32 + l%32 of a tap: their slots are equal (32 is a multiple
+  // of the permutation's period)
+  const int wrow = lane & 31;
+  const int bbase = D::kABytes + (wrow * KG + D::slot(wrow, kg)) * 16 + h * 8;
+  v16i acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = v16i{};
+  // multiplies chunk cc from buffer b; the codes of chunk cc + 1 (r) go to the other
+  // buffer piece by piece between the taps, each reloaded with chunk cc + 3
+  auto chunk = [&](int cc, int b, Regs& r) __attribute__((always_inline)) {
+    const uint8_t* buf = lds + b * D::kBuf;
+#pragma unroll
+    for (int tap = 0; tap < 9; ++tap) {
+      v4i fa[2], fb[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) fa[i] = *reinterpret_cast<const v4i*>(buf + atap[tap][i]);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const v2u32 wr = *reinterpret_cast<const v2u32*>(buf + bbase + (tap * 64 + j * 32) * 16 * KG);
+        uint32_t w0, w1, w2, w3;
+        expand_int4<WSIGNED>(wr[0], w0, w1);
+        expand_int4<WSIGNED>(wr[1], w2, w3);
+        fb[j] = v4i{(int)w0, (int)w1, (int)w2, (int)w3};
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fb[j], fa[i], acc[i][j], 0, 0, 0);
+      if (tap < D::kBPieces) {
+        store_w(r, b ^ 1, tap);
+        load_w(r, cc + 3, tap);
+      }
+      if (tap >= 9 - 2 * D::kAPieces && (tap & 1)) {
+        constexpr int q0 = 9 - 2 * D::kAPieces;
+        store_g(r, b ^ 1, (tap - q0) >> 1);
+        load_g(r, cc + 3, (tap - q0) >> 1);
+      }
+    }
+    __syncthreads();
+  };
+
+#pragma unroll
+  for (int q = 0; q < D::kBPieces; ++q) store_w(r0, 0, q);
+#pragma unroll
+  for (int q = 0; q < D::kAPieces; ++q) store_g(r0, 0, q);
+  load(r0, 2);
+  __syncthreads();
+  int cc = 0;
+  for (; cc + 2 <= nchunks; cc += 2) {
+    chunk(cc, 0, r1);
+    chunk(cc + 1, 1, r0);
+  }
+  if (cc < nchunks) chunk(cc, 0, r1);
+
+  // epilogue through LDS slabs of 32 pixels x 64 channels a wave: lane l holds
+  // pixel l%32 and, in registers 4q..4q+3 of tile j, channels 32j + 8q + 4h + 0..3.
+  // The waves of a pixel group store 32 / KG rows each, adding the KG slabs (16
+  // lanes per row, 4 rows per instruction).
+  const float sc = epilogue_scale<kAcLuq, NS, WSIGNED>(*a.alpha, *a.wscale);
+  static_assert(8 * 32 * kConvEP * 4 <= 2 * D::kBuf, "epilogue slabs fit");
+  int32_t* E = reinterpret_cast<int32_t*>(lds) + wave * 32 * kConvEP;
+  const int32_t* E0 = reinterpret_cast<const int32_t*>(lds) + wp * 32 * kConvEP;
+  const int scol = (lane & 15) * 4, c = c0 + scol;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        *reinterpret_cast<v4i*>(E + (lane & 31) * kConvEP + j * 32 + 8 * q + 4 * h) =
+            v4i{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+    __syncthreads();
+#pragma unroll
+    for (int rr = 0; rr < 32 / KG; rr += 4) {
+      const int sr = kg * (32 / KG) + rr + (lane >> 4);
+      const int t = t0 + wp * 64 + i * 32 + sr;
+      if (t < a.T && c < a.C) {
+        v4i x = *reinterpret_cast<const v4i*>(E0 + sr * kConvEP + scol);
+#pragma unroll
+        for (int g = 1; g < KG; ++g) x += *reinterpret_cast<const v4i*>(E0 + (g * PX * 32 + sr) * kConvEP + scol);
+        v4u v;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = __float_as_uint(__fmul_rn((float)x[k], sc));
+        float* dst = a.dact + (int64_t)t * a.C + c;
+        if (a.vec) {
+          *reinterpret_cast<v4u*>(dst) = v;
+        } else {
+#pragma unroll
+          for (int k = 0; k < 4; ++k)
+            if (c + k < a.C) dst[k] = __uint_as_float(v[k]);
+        }
+      }
+    }
+    __syncthreads();  // the slabs are rewritten by the next i
+  }
+}
+
+template <int NS>
+static void conv_dd_launch(ConvArgs a, int wsigned, hipStream_t st) {
+  a.tiles_m = (a.T + kDdBM - 1) / kDdBM;
+  const dim3 grid((unsigned)(a.tiles_m * ((a.C + kConvBN - 1) / kConvBN)));
+  if (wsigned)
+    hipLaunchKernelGGL((conv3x3_dgrad_deep_kernel<NS, true>), grid, dim3(kDdThreads), 0, st, a);
+  else
+    hipLaunchKernelGGL((conv3x3_dgrad_deep_kernel<NS, false>), grid, dim3(kDdThreads), 0, st, a);
+}
+
+// ---------------------------------------------------------------------------
 // Activation gradient, row form (W <= 64, Cout 32 or 64, C a multiple of 32):
 // output image row (b, y) reads the gradient rows y - 1, y, y + 1 of its own
 // image and nothing else, so a workgroup walks a run of consecutive image
@@ -576,6 +835,15 @@ hipError_t launch_conv3x3_dgrad(const uint8_t* g, int64_t g_plane, int ns, const
       if (Cout == 64) conv_dr_launch<2, 2>(d, w_signed, grid, st);
       else conv_dr_launch<2, 1>(d, w_signed, grid, st);
     }
+    return hipGetLastError();
+  }
+  // the deep form wherever its workgroups (one per CU) fit the chip at once: on
+  // 15 such layers of 96 to 512 output channels it took 0.54 to 0.89 of the tile
+  // form's time; in two rounds it loses (64 x 14 x 14, 256 -> 256, 392 workgroups:
+  // 20.4 against 16.3 us)
+  if (Cout > 64 && W <= kDdMaxW && (a.T + kDdBM - 1) / kDdBM * ((C + kConvBN - 1) / kConvBN) <= 256) {
+    if (ns == 1) conv_dd_launch<1>(a, w_signed, st);
+    else conv_dd_launch<2>(a, w_signed, st);
     return hipGetLastError();
   }
   // persistent workgroups: about two per CU (one for wide images), a multiple

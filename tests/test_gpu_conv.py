@@ -92,6 +92,13 @@ def _conv_case(L, B, H, W, C, Cout, ns=1, wsig=True, seed=0, zero_grad=False, us
     (2, 45, 1, 16, 64),       # width 1
     (160, 32, 32, 8, 96),     # 640 tiles: workgroups walk two tiles, two Cout chunks each
     (8, 90, 100, 8, 96),      # wide-halo kernel with workgroups walking two tiles
+    # deep form (Cout above 64, at most 62 pixels wide)
+    (8, 4, 4, 64, 128),       # 128 pixels: exactly one tile
+    (3, 43, 1, 40, 96),       # 129 pixels, width 1, a half-filled last chunk, a partial channel tile
+    (32, 7, 7, 96, 512),      # eight chunks
+    (5, 9, 62, 34, 160),      # the widest image of the deep form, C not a multiple of 4
+    (2, 3, 63, 64, 128),      # just past it: the tile form
+    (1, 2, 256, 70, 192),     # the widest image accepted, two pixel tiles of one image row each side
     # row form (W <= 64, Cout 32 or 64, C a multiple of 32)
     (2, 9, 56, 64, 64),       # two pixel tiles per row, the second ragged
     (3, 5, 64, 96, 32),       # width 64, one k-step per tap, a half-empty second channel block
@@ -109,7 +116,7 @@ def test_conv_dgrad_parity(L, B, H, W, C, Cout, ns):
     _conv_case(L, B, H, W, C, Cout, ns=ns, seed=B * 1000 + H * 100 + W + C + Cout)
 
 
-@pytest.mark.parametrize("B,H,W,C,Cout", [(2, 7, 9, 24, 64), (1, 6, 70, 8, 96), (2, 9, 56, 64, 64),
+@pytest.mark.parametrize("B,H,W,C,Cout", [(2, 7, 9, 24, 64), (1, 6, 70, 8, 96), (2, 7, 9, 64, 256), (2, 9, 56, 64, 64),
                                           (3, 4, 30, 64, 32)])
 def test_conv_dgrad_unsigned_weights(L, B, H, W, C, Cout):
     _conv_case(L, B, H, W, C, Cout, wsig=False, seed=17)
