@@ -658,42 +658,58 @@ struct GemmPlan {
 // The tile and the number of splits with the least predicted time.  A split's k
 // range is a multiple of the tile's stage depth; min_splits keeps a chunk's int32
 // sums exact.
-static GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int64_t max_exact_k) {
+static GemmPlan search_plan(int64_t M, int64_t N, int64_t K, int64_t max_exact_k) {
   GemmPlan best{};
   float best_cost = 0.0f;
-  const int64_t min_splits = K <= max_exact_k ? 1 : (K + max_exact_k - 1) / max_exact_k;
+  const int min_splits = K <= max_exact_k ? 1 : (int)((K + max_exact_k - 1) / max_exact_k);
+  const float split_out = kSplitCostPerMOut * 1e-6f * (float)(M * N);   // per split
   for (int t = 0; t < kGemmTiles; ++t) {
     const TileCost& c = kTileCost[t];
     auto ceil_shift = [](int64_t v, int l) { return (v + ((int64_t)1 << l) - 1) >> l; };
     const int64_t tiles_m = ceil_shift(M, c.lm), tiles_n = ceil_shift(N, c.ln), nt = tiles_m * tiles_n;
-    const int64_t stages = ceil_shift(K, c.lk);
-    auto consider = [&](int64_t want) {
+    const int stages = (int)ceil_shift(K, c.lk);   // K < 2^31 (operands stay below 2 GiB)
+    auto consider = [&](int want) {
       if (want < min_splits) want = min_splits;
       if (want > stages) want = stages;
-      const int64_t chunk = want == 1 ? stages : (stages + want - 1) / want;
-      const int64_t splits = want == 1 ? 1 : (stages + chunk - 1) / chunk;
-      const float s = (float)(chunk << c.lk) * (1.0f / 128);
+      const int chunk = want == 1 ? stages : (stages + want - 1) / want;
+      const int splits = want == 1 ? 1 : (stages + chunk - 1) / chunk;
+      const float s = (float)((int64_t)chunk << c.lk) * (1.0f / 128);
       const int64_t nb = nt * splits;
       // workgroups per CU: between the mean and the busiest CU's
       const float mean = nb < kCus ? 1.0f : (float)nb * (1.0f / kCus);
       const float per_cu = 0.5f * (mean + (float)((nb + kCus - 1) / kCus));
       const float alone = s * c.stage1 + c.fixed1, shared = per_cu * (s * c.stage + c.fixed);
       float cost = alone > shared ? alone : shared;
-      if (splits > 1) cost += kSplitCost + kSplitCostPerMOut * 1e-6f * (float)(M * N) * (float)splits;
+      if (splits > 1) cost += kSplitCost + split_out * (float)splits;
       if (best.splits == 0 || cost < best_cost) {
         best_cost = cost;
-        best = GemmPlan{(GemmTile)t, tiles_m, tiles_n, (int)splits, chunk << c.lk};
+        best = GemmPlan{(GemmTile)t, tiles_m, tiles_n, splits, (int64_t)chunk << c.lk};
       }
     };
     consider(1);
     // splits only where the tiles leave CUs idle (up to two workgroups per CU)
-    // and the reduction's launch does not cost more than there is to gain
-    if (nt < kCus && stages > 1 && best_cost > kSplitCost + c.fixed1) {
-      for (int64_t s = 2; s * nt < 2 * kCus && s <= stages; s *= 2) consider(s);
-      consider(kCus / nt);
+    // and two of them alone do not cost more than there is to gain
+    const float least = kSplitCost + 2 * split_out + c.fixed1;
+    if (nt < kCus && stages > 1 && best_cost > least) {
+      for (int s = 2; s * nt < 2 * kCus && s <= stages; s *= 2) consider(s);
+      consider(kCus / (int)nt);
     }
   }
   return best;
+}
+
+// The plan of the calling thread's last shape is kept: a call asks for it up to
+// three times (workspace size, its check, the launch), and the search costs 0.1 to
+// 0.5 us of host time.
+static GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int64_t max_exact_k) {
+  struct Last {
+    int64_t M, N, K, exact;
+    GemmPlan plan;
+  };
+  static thread_local Last last{0, 0, 0, 0, {}};
+  if (last.M != M || last.N != N || last.K != K || last.exact != max_exact_k)
+    last = Last{M, N, K, max_exact_k, search_plan(M, N, K, max_exact_k)};
+  return last.plan;
 }
 
 template <typename S, int AC, int NS, bool BSIGNED>
