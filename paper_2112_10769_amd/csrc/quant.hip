@@ -159,6 +159,17 @@ __global__ __launch_bounds__(1024) void fold_partials_kernel(const uint32_t* __r
 // smaller tiles in flight; the INT4 encoder is bound by memory and prefers
 // longer contiguous stores.
 constexpr int kLuqTileLg = 12, kInt4TileLg = 13;
+// Smallest tiles (words): two trips for the pipelined LUQ loop, one for INT4
+// (512 x 4608 fp32: 11.5 -> 10.4 us against 1024 words).
+constexpr int kLuqTileMinLg = 10, kInt4TileMinLg = 9;
+// Tensors up to kSmallBytes are bound by the latency of their own few loads and
+// stores rather than by memory: their max pass takes fewer loads per thread (more
+// blocks), and their tiles 16 column groups instead of 32, which makes the
+// transposed runs of a tile twice as long.  Larger tensors measured slower with
+// either inside a training step (8192 x 2048 fp32, max pass 17.0 against 17.8 us,
+// INT4 encode 15.7 against 18.5).
+constexpr int64_t kSmallBytes = 16LL << 20;
+constexpr int kSmallTileMaxLg = 4, kTileMaxLg = 5;
 constexpr int kTilePad = 4;  // LDS words between column groups (keeps 16-byte alignment)
 
 //
@@ -166,124 +177,118 @@ constexpr int kTilePad = 4;  // LDS words between column groups (keeps 16-byte a
 // of an item become 8 bytes of sums (elements 0..3 in the first word), which
 // take the places of the two planes in LDS; phase B transposes 4x4 byte
 // blocks and stores 8 bytes (8 rows) per column.
-template <int NS, typename Enc, bool SUM = false>
-__device__ __forceinline__ void encode_tiles(const Enc& enc, int64_t rows, int64_t cols, int lg,
-                                             int lt, uint8_t* codes, uint8_t* codes_t,
-                                             int64_t plane, uint32_t* lds, uint32_t& mx) {
+// Work goes by trips of two items per thread.  A block's first trip can be loaded
+// before the block folds the partial maxima, so that the two latencies overlap;
+// it is handed to encode_tiles.
+constexpr int kTripItems = 2;
+
+struct TileGrid {
+  int64_t rows, cols, cgs, ntc, total;
+  int lg, lt, tg, tr;
+  __device__ __forceinline__ TileGrid(int64_t rows_, int64_t cols_, int lg_, int lt_)
+      : rows(rows_), cols(cols_), cgs(cols_ >> 3), lg(lg_), lt(lt_), tg(1 << lg_), tr((1 << lt_) >> lg_) {
+    ntc = (cgs + tg - 1) / tg;
+    total = ((rows + tr - 1) / tr) * ntc;
+  }
+};
+
+struct Trip {
+  int g[kTripItems], r[kTripItems];
+  bool ok[kTripItems];
+  int64_t e0[kTripItems];
+  U8 v[kTripItems];
+};
+
+// Items trip * kTripItems .. of the tile at (r0, g0).  Without a branch an item off
+// the tensor reads element 0 and is dropped; COND loads only the items on it.
+template <bool BF16, bool NT, bool COND>
+__device__ __forceinline__ void fetch_trip(Trip& T, const void* x, const TileGrid& t, int64_t r0, int64_t g0,
+                                           int trip) {
+#pragma unroll
+  for (int u = 0; u < kTripItems; ++u) {
+    const int q = threadIdx.x + (trip * kTripItems + u) * kThreads;
+    T.g[u] = q & (t.tg - 1);
+    T.r[u] = q >> t.lg;
+    const int64_t row = r0 + T.r[u], cg = g0 + T.g[u];
+    T.ok[u] = row < t.rows && cg < t.cgs;
+    T.e0[u] = row * t.cols + cg * 8;
+    if constexpr (COND) {
+      if (T.ok[u]) T.v[u] = load8<BF16, NT>(x, T.e0[u]);
+    } else {
+      T.v[u] = load8<BF16, NT>(x, T.ok[u] ? T.e0[u] : 0);
+    }
+  }
+}
+
+// First trip of the block's first tile (a grid has at most as many blocks as
+// tiles); a streamed tensor is walked from its end.
+template <bool BF16, bool NT>
+__device__ __forceinline__ void first_trip(Trip& T, const void* x, const TileGrid& t) {
+  const int64_t k = NT ? t.total - 1 - (int64_t)blockIdx.x : (int64_t)blockIdx.x;
+  fetch_trip<BF16, NT, false>(T, x, t, (k / t.ntc) * t.tr, (k % t.ntc) * t.tg, 0);
+}
+
+// AHEAD: ta holds the first trip of the block's first tile.
+template <int NS, typename Enc, bool AHEAD, bool SUM = false>
+__device__ __forceinline__ void encode_tiles(const Enc& enc, const TileGrid& tile, Trip& ta, uint8_t* codes,
+                                             uint8_t* codes_t, int64_t plane, uint32_t* lds, uint32_t& mx) {
+  const int64_t rows = tile.rows, cols = tile.cols;
+  const int lg = tile.lg, lt = tile.lt;
   static_assert(!SUM || NS == 2, "the summed operand takes two samples");
-  const int tw = 1 << lt, tg = 1 << lg, tr = tw >> lg, pitch = tr + kTilePad;
-  const int64_t cgs = cols >> 3;
-  const int64_t ntr = (rows + tr - 1) / tr, ntc = (cgs + tg - 1) / tg;
-  for (int64_t k = blockIdx.x; k < ntr * ntc; k += gridDim.x) {
-    const int64_t t = Enc::kNT ? ntr * ntc - 1 - k : k;  // a streamed tensor is walked from its end
+  const int tw = 1 << lt, tg = tile.tg, tr = tile.tr, pitch = tr + kTilePad;
+  const int64_t cgs = tile.cgs, ntc = tile.ntc, total = tile.total;
+  constexpr int U = kTripItems;
+  const int ntrips = tw / (U * kThreads);
+  auto encode = [&](const Trip& T) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if constexpr (Enc::kTrack) {
+        if (T.ok[u]) mx = max(mx, max_key8(T.v[u]));
+      }
+      uint32_t w[NS];
+#pragma unroll
+      for (int s = 0; s < NS; ++s) w[s] = 0;
+      if (T.ok[u]) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s) w[s] = enc.word(T.v[u], (uint64_t)(T.e0[u] >> 3), s);
+        if constexpr (SUM) {
+          uint32_t lo, hi;
+          smp_sum_bytes(w[0], w[1], lo, hi);
+          w[0] = lo;
+          w[1] = hi;
+          if (codes) store_word2<Enc::kNTStore>(codes + T.e0[u], lo, hi);
+        } else {
+#pragma unroll
+          for (int s = 0; s < NS; ++s)
+            if (codes) store_word<Enc::kNTStore>(codes + s * plane + (T.e0[u] >> 1), w[s]);
+        }
+      }
+#pragma unroll
+      for (int s = 0; s < NS; ++s) lds[(s * tg + T.g[u]) * pitch + T.r[u]] = w[s];
+    }
+  };
+  for (int64_t k = blockIdx.x; k < total; k += gridDim.x) {
+    const int64_t t = Enc::kNT ? total - 1 - k : k;  // a streamed tensor is walked from its end
     const int64_t r0 = (t / ntc) * tr, g0 = (t % ntc) * tg;
+    if (!AHEAD || k != (int64_t)blockIdx.x) enc.fetch(ta, tile, r0, g0, 0);
     if constexpr (Enc::kPipeline) {
-      // two items per trip (tw is a multiple of 2 * kThreads, so the trip count
-      // is even): the next trip's loads are issued before this trip's items are
-      // encoded, so one trip's encode hides the next one's memory latency.  The
-      // fetch after the last trip re-reads the first one (in bounds, ignored):
-      // every trip issues the same loads and the wait counts stay static.
-      constexpr int U = 2;
-      const int ntrips = tw / (U * kThreads);
-      struct Trip {
-        int g[U], r[U];
-        bool ok[U];
-        int64_t e0[U];
-        U8 v[U];
-      };
-      auto fetch = [&](Trip& T, int trip) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int q = threadIdx.x + (trip * U + u) * kThreads;
-          T.g[u] = q & (tg - 1);
-          T.r[u] = q >> lg;
-          const int64_t row = r0 + T.r[u], cg = g0 + T.g[u];
-          T.ok[u] = row < rows && cg < cgs;
-          T.e0[u] = row * cols + cg * 8;
-          T.v[u] = enc.load(T.ok[u] ? T.e0[u] : 0);  // no branch: an item off the tensor reads element 0
-        }
-      };
-      auto encode = [&](const Trip& T) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          if constexpr (Enc::kTrack) {
-            if (T.ok[u]) mx = max(mx, max_key8(T.v[u]));
-          }
-          uint32_t w[NS];
-#pragma unroll
-          for (int s = 0; s < NS; ++s) w[s] = 0;
-          if (T.ok[u]) {
-#pragma unroll
-            for (int s = 0; s < NS; ++s) w[s] = enc.word(T.v[u], (uint64_t)(T.e0[u] >> 3), s);
-            if constexpr (SUM) {
-              uint32_t lo, hi;
-              smp_sum_bytes(w[0], w[1], lo, hi);
-              w[0] = lo;
-              w[1] = hi;
-              if (codes) store_word2<Enc::kNTStore>(codes + T.e0[u], lo, hi);
-            } else {
-#pragma unroll
-              for (int s = 0; s < NS; ++s)
-                if (codes) store_word<Enc::kNTStore>(codes + s * plane + (T.e0[u] >> 1), w[s]);
-            }
-          }
-#pragma unroll
-          for (int s = 0; s < NS; ++s) lds[(s * tg + T.g[u]) * pitch + T.r[u]] = w[s];
-        }
-      };
-      Trip ta, tb;
-      fetch(ta, 0);
+      // the next trip's loads are issued before this trip's items are encoded, so
+      // one trip's encode hides the next one's memory latency (tw is a multiple
+      // of 4 * kThreads, so the trip count is even).  The fetch after the last
+      // trip re-reads the first one (in bounds, ignored): every trip issues the
+      // same loads and the wait counts stay static.
+      Trip tb;
       for (int trip = 0; trip < ntrips; trip += 2) {
-        fetch(tb, trip + 1);
+        enc.fetch(tb, tile, r0, g0, trip + 1);
         encode(ta);
-        fetch(ta, trip + 2 < ntrips ? trip + 2 : 0);
+        enc.fetch(ta, tile, r0, g0, trip + 2 < ntrips ? trip + 2 : 0);
         encode(tb);
       }
     } else {
-      // two items per trip (tw is a multiple of 2 * kThreads): both loads are
-      // in flight before either is encoded
-      constexpr int U = 2;
-      for (int q0 = threadIdx.x; q0 < tw; q0 += U * kThreads) {
-        int g[U], r[U];
-        bool ok[U];
-        int64_t e0[U];
-        U8 v[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const int q = q0 + u * kThreads;
-          g[u] = q & (tg - 1);
-          r[u] = q >> lg;
-          const int64_t row = r0 + r[u], cg = g0 + g[u];
-          ok[u] = row < rows && cg < cgs;
-          e0[u] = row * cols + cg * 8;
-          if (ok[u]) {
-            v[u] = enc.load(e0[u]);
-            if constexpr (Enc::kTrack) mx = max(mx, max_key8(v[u]));
-          }
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          uint32_t w[NS];
-#pragma unroll
-          for (int s = 0; s < NS; ++s) w[s] = 0;
-          if (ok[u]) {
-#pragma unroll
-            for (int s = 0; s < NS; ++s) w[s] = enc.word(v[u], (uint64_t)(e0[u] >> 3), s);
-            if constexpr (SUM) {
-              uint32_t lo, hi;
-              smp_sum_bytes(w[0], w[1], lo, hi);
-              w[0] = lo;
-              w[1] = hi;
-              if (codes) store_word2<Enc::kNTStore>(codes + e0[u], lo, hi);
-            } else {
-#pragma unroll
-              for (int s = 0; s < NS; ++s)
-                if (codes) store_word<Enc::kNTStore>(codes + s * plane + (e0[u] >> 1), w[s]);
-            }
-          }
-#pragma unroll
-          for (int s = 0; s < NS; ++s) lds[(s * tg + g[u]) * pitch + r[u]] = w[s];
-        }
+      encode(ta);
+      for (int trip = 1; trip < ntrips; ++trip) {
+        enc.fetch(ta, tile, r0, g0, trip);
+        encode(ta);
       }
     }
     __syncthreads();
@@ -670,7 +675,9 @@ struct LuqEnc {
   static constexpr bool kNTStore = NT;
   const LuqArgs* a;
   const LuqParams* p;
-  __device__ U8 load(int64_t e0) const { return load8<BF16, NT>(a->g, e0); }
+  __device__ __forceinline__ void fetch(Trip& T, const TileGrid& t, int64_t r0, int64_t g0, int trip) const {
+    fetch_trip<BF16, NT, false>(T, a->g, t, r0, g0, trip);
+  }
   __device__ uint32_t word(const U8& v, uint64_t blk, int s) const {
     return p->zero ? 0u : luq_code_word<BF16, SCALED, HS>(v, blk, s, *a, *p);
   }
@@ -679,14 +686,18 @@ struct LuqEnc {
 template <bool BF16, bool NT, int NS, bool HS = false, bool SUM = false>
 __global__ __launch_bounds__(kThreads) void luq_encode_tile_kernel(LuqArgs a, int lg, int lt) {
   __shared__ __attribute__((aligned(16))) uint32_t lds[NS * ((1 << kLuqTileLg) + 32 * kTilePad)];
+  const TileGrid tile(a.rows, a.cols, lg, lt);
+  Trip first;
+  // (loading the first trip before the fold, as the INT4 encoder does, took 8192 x
+  // 16384 bf16 from 139.6 to 142.4 us and 2048 x 4096 from 16.2 to 16.8)
   const LuqParams p = luq_block_params<HS>(a);
   uint32_t mx = 0;
   if (p.S != 1.0f)
-    encode_tiles<NS, LuqEnc<BF16, NT, true, HS>, SUM>(LuqEnc<BF16, NT, true, HS>{&a, &p}, a.rows, a.cols, lg, lt,
-                                                      a.codes, a.codes_t, a.plane, lds, mx);
+    encode_tiles<NS, LuqEnc<BF16, NT, true, HS>, false, SUM>(LuqEnc<BF16, NT, true, HS>{&a, &p}, tile, first, a.codes,
+                                                      a.codes_t, a.plane, lds, mx);
   else
-    encode_tiles<NS, LuqEnc<BF16, NT, false, HS>, SUM>(LuqEnc<BF16, NT, false, HS>{&a, &p}, a.rows, a.cols, lg, lt,
-                                                       a.codes, a.codes_t, a.plane, lds, mx);
+    encode_tiles<NS, LuqEnc<BF16, NT, false, HS>, false, SUM>(LuqEnc<BF16, NT, false, HS>{&a, &p}, tile, first, a.codes,
+                                                       a.codes_t, a.plane, lds, mx);
   if (HS) write_block_max(mx, a.part_out);
 }
 
@@ -826,16 +837,23 @@ struct Int4Enc {
   static constexpr bool kNTStore = false;
   const Int4Args* a;
   const Int4Params* p;
-  __device__ U8 load(int64_t e0) const { return load8<BF16, NT>(a->x, e0); }
+  __device__ __forceinline__ void fetch(Trip& T, const TileGrid& t, int64_t r0, int64_t g0, int trip) const {
+    fetch_trip<BF16, NT, NT>(T, a->x, t, r0, g0, trip);
+  }
   __device__ uint32_t word(const U8& v, uint64_t, int) const { return p->zero ? 0u : int4_word(v, *p); }
 };
 
 template <bool BF16, bool NT>
 __global__ __launch_bounds__(kThreads) void int4_encode_tile_kernel(Int4Args a, int lg, int lt) {
   __shared__ __attribute__((aligned(16))) uint32_t lds[(1 << kInt4TileLg) + 32 * kTilePad];
+  const TileGrid tile(a.rows, a.cols, lg, lt);
+  Trip first;
+  // the fold overlaps the first trip's loads, except for streamed tensors (16384
+  // x 4096 fp32: 107.2 against 110.6 us)
+  if constexpr (!NT) first_trip<BF16, NT>(first, a.x, tile);
   const Int4Params p = int4_block_params(a);
   uint32_t unused = 0;
-  encode_tiles<1>(Int4Enc<BF16, NT>{&a, &p}, a.rows, a.cols, lg, lt, a.codes, a.codes_t, 0, lds, unused);
+  encode_tiles<1, Int4Enc<BF16, NT>, !NT>(Int4Enc<BF16, NT>{&a, &p}, tile, first, a.codes, a.codes_t, 0, lds, unused);
 }
 
 // Small tensors (up to kInt4SmallN elements, such as a convolution's weight):
@@ -879,7 +897,10 @@ __global__ __launch_bounds__(kThreads) void int4_small_kernel(Int4Args a, int lg
   const Int4Params p = int4_params(a, m);
   if (a.codes_t) {
     uint32_t unused = 0;
-    encode_tiles<1>(Int4Enc<BF16, false>{&a, &p}, a.rows, a.cols, lg, lt, a.codes, a.codes_t, 0, lds, unused);
+    const TileGrid tile(a.rows, a.cols, lg, lt);
+    Trip first;
+    first_trip<BF16, false>(first, a.x, tile);
+    encode_tiles<1, Int4Enc<BF16, false>, true>(Int4Enc<BF16, false>{&a, &p}, tile, first, a.codes, a.codes_t, 0, lds, unused);
     return;
   }
   const int64_t ngroups = (a.n + 7) >> 3;
@@ -898,12 +919,15 @@ __global__ __launch_bounds__(kThreads) void int4_small_kernel(Int4Args a, int lg
 
 // Every encode block folds the partials it is given before it starts, so
 // while they are given directly their count is kept proportional to the
-// tensor (at least 16 groups of 8 elements per max-pass thread); large
-// tensors get up to kMaxPartials blocks (8 groups per thread) and one fold.
-static int max_pass_blocks(int64_t n) {
+// tensor: four groups of 8 elements per max-pass thread for small tensors (256 x 512
+// fp32: 8.6 -> 8.0 us for the whole quantizer, 1184 x 1000: 10.7 -> 9.3), else
+// sixteen; large tensors get up to kMaxPartials blocks (8 groups per thread) and
+// one fold.
+static int max_pass_blocks(int64_t n, bool bf16) {
   const int64_t groups = (n + 7) >> 3;
-  int64_t b = (groups + kThreads * 16 - 1) / (kThreads * 16);
-  if (b > kDirectPartials) b = (groups + kThreads * 8 - 1) / (kThreads * 8);
+  auto blocks = [&](int per) { return (groups + kThreads * per - 1) / (kThreads * per); };
+  int64_t b = blocks(n * (bf16 ? 2 : 4) <= kSmallBytes ? 4 : 16);
+  if (b > kDirectPartials) b = blocks(8);
   if (b < 1) b = 1;
   if (b > kMaxPartials) b = kMaxPartials;
   return (int)b;
@@ -935,7 +959,7 @@ static int64_t tile_count(int64_t rows, int64_t cols, int lg, int lt) {
   return ((rows + tr - 1) / tr) * (((cols >> 3) + tg - 1) / tg);
 }
 
-static TileShape tile_shape(int64_t rows, int64_t cols, int max_lt) {
+static TileShape tile_shape(int64_t rows, int64_t cols, int max_lt, int min_lt, int max_lg) {
   // Narrow matrices (at most 8 column groups, e.g. a convolution's 64
   // channels) have tall tiles whose count rarely divides the 256 compute units
   // evenly: there, twice as many smaller tiles go to at most 1024 persistent
@@ -947,9 +971,9 @@ static TileShape tile_shape(int64_t rows, int64_t cols, int max_lt) {
   const int64_t want = narrow ? 1536 : 768;
   TileShape t;
   t.lg = 0;
-  while (t.lg < 5 && (1LL << t.lg) < cgs) ++t.lg;
+  while (t.lg < max_lg && (1LL << t.lg) < cgs) ++t.lg;
   t.lt = max_lt;
-  while (t.lt > 10 && t.lt - 1 - t.lg >= 3 && tile_count(rows, cols, t.lg, t.lt) < want) --t.lt;
+  while (t.lt > min_lt && t.lt - 1 - t.lg >= 3 && tile_count(rows, cols, t.lg, t.lt) < want) --t.lt;
   int64_t b = tile_count(rows, cols, t.lg, t.lt);
   if (b < 1) b = 1;
   if (b > kMaxEncodeBlocks) b = kMaxEncodeBlocks;
@@ -989,8 +1013,9 @@ static bool stream_reads(int64_t n, bool bf16) { return n * (bf16 ? 2 : 4) > kCa
 // ns: 1 or 2 sample planes, or kSmpSum (two samples stored as int8 sums).
 template <bool BF16, bool NT, bool HS>
 static int luq_encode_launch(const LuqArgs& a, int ns, hipStream_t st) {
+  const bool small = a.n * (BF16 ? 2 : 4) <= kSmallBytes;
   if (a.codes_t) {
-    const TileShape t = tile_shape(a.rows, a.cols, kLuqTileLg);
+    const TileShape t = tile_shape(a.rows, a.cols, kLuqTileLg, kLuqTileMinLg, small ? kSmallTileMaxLg : kTileMaxLg);
     if (ns == 1)
       hipLaunchKernelGGL((luq_encode_tile_kernel<BF16, NT, 1, HS>), dim3(t.blocks), dim3(kThreads), 0, st, a, t.lg,
                          t.lt);
@@ -1054,7 +1079,7 @@ hipError_t launch_luq_quantize(const void* g, int bf16, int64_t rows, int64_t co
   a.k1 = (uint32_t)(seed >> 32);
   a.counter = counter;
   a.partial = static_cast<uint32_t*>(ws);
-  a.nparts = max_pass_blocks(n);
+  a.nparts = max_pass_blocks(n, bf16 != 0);
   a.codes = codes;
   a.codes_t = codes_t;
   a.plane = (int64_t)plane_bytes(n);
@@ -1159,7 +1184,7 @@ hipError_t launch_luq_quantize_hindsight(const void* g, int bf16, int64_t rows, 
 template <bool BF16>
 static hipError_t int4_launch_t(Int4Args a, hipStream_t st) {
   if (a.n <= kInt4SmallN) {
-    const TileShape t = tile_shape(a.rows, a.cols, kInt4TileLg);
+    const TileShape t = tile_shape(a.rows, a.cols, kInt4TileLg, kInt4TileMinLg, kSmallTileMaxLg);
     int blocks = a.codes_t ? t.blocks : (int)((((a.n + 7) >> 3) + kThreads - 1) / kThreads);
     if (blocks > kInt4SmallBlocks) blocks = kInt4SmallBlocks;
     if (a.is_signed)
@@ -1177,7 +1202,8 @@ static hipError_t int4_launch_t(Int4Args a, hipStream_t st) {
   }
   const bool nt = a.n * (BF16 ? 2 : 4) > kInt4StreamBytes;
   if (a.codes_t) {
-    const TileShape t = tile_shape(a.rows, a.cols, kInt4TileLg);
+    const TileShape t = tile_shape(a.rows, a.cols, kInt4TileLg, kInt4TileMinLg,
+                                   a.n * (BF16 ? 2 : 4) <= kSmallBytes ? kSmallTileMaxLg : kTileMaxLg);
     if (nt)
       hipLaunchKernelGGL((int4_encode_tile_kernel<BF16, true>), dim3(t.blocks), dim3(kThreads), 0, st, a, t.lg, t.lt);
     else
@@ -1208,7 +1234,7 @@ hipError_t launch_int4_quantize(const void* x, int bf16, int64_t rows, int64_t c
   a.is_signed = is_signed;
   a.clip = clip;
   a.partial = static_cast<uint32_t*>(ws);
-  a.nparts = max_pass_blocks(n);
+  a.nparts = max_pass_blocks(n, bf16 != 0);
   a.codes = codes;
   a.codes_t = codes_t;
   a.scale_out = scale;
