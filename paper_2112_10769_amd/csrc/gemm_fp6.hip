@@ -275,7 +275,7 @@ __global__ __launch_bounds__(256, 1) void gemm_fp6_kernel(Fp6GemmArgs a) {
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
 
-  // Epilogue through LDS, as gemm_luq_int4_kernel's: lane l of MFMA tile
+  // Epilogue through LDS, as gemm_tile_kernel's: lane l of MFMA tile
   // (i, j) holds row l%32 and, in registers 4q..4q+3, columns
   // 8q + 4 (l/32) + 0..3.  The fp32 sums times kToCarrier are the INT8
   // carrier's integer sums (exact), scaled by the same fp32 factor.
