@@ -12,8 +12,9 @@
 // is formed: the output is T x C floats, not T x 9C.
 //
 // Tile form (any shape; images of at most 64 pixels with Cout 32 or 64 and C a
-// multiple of 32 take the row form further down): a tile is kBM consecutive
-// pixels times 64 channels.  For each 64-deep chunk of Cout a workgroup
+// multiple of 32 take the row form further down, small layers of more than 64
+// output channels the deep form): a tile is kBM consecutive pixels times 64
+// channels.  For each 64-deep chunk of Cout a workgroup
 // expands into LDS:
 //   - the gradient codes of the tile's pixels and of the W + 1 pixels on
 //     either side (every tap of every pixel reads inside that halo, because a

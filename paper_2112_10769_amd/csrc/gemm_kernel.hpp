@@ -661,19 +661,20 @@ struct GemmPlan {
 static GemmPlan search_plan(int64_t M, int64_t N, int64_t K, int64_t max_exact_k) {
   GemmPlan best{};
   float best_cost = 0.0f;
-  const int min_splits = K <= max_exact_k ? 1 : (int)((K + max_exact_k - 1) / max_exact_k);
-  const float split_out = kSplitCostPerMOut * 1e-6f * (float)(M * N);   // per split
+  const int64_t min_splits = K <= max_exact_k ? 1 : (K - 1) / max_exact_k + 1;
+  const float split_out = kSplitCostPerMOut * 1e-6f * (float)M * (float)N;   // per split
   for (int t = 0; t < kGemmTiles; ++t) {
     const TileCost& c = kTileCost[t];
-    auto ceil_shift = [](int64_t v, int l) { return (v + ((int64_t)1 << l) - 1) >> l; };
+    // (the workspace query takes any sizes: no overflow for v up to INT64_MAX)
+    auto ceil_shift = [](int64_t v, int l) { return ((v - 1) >> l) + 1; };
     const int64_t tiles_m = ceil_shift(M, c.lm), tiles_n = ceil_shift(N, c.ln), nt = tiles_m * tiles_n;
-    const int stages = (int)ceil_shift(K, c.lk);   // K < 2^31 (operands stay below 2 GiB)
-    auto consider = [&](int want) {
+    const int64_t stages = ceil_shift(K, c.lk);
+    auto consider = [&](int64_t want) {
       if (want < min_splits) want = min_splits;
       if (want > stages) want = stages;
-      const int chunk = want == 1 ? stages : (stages + want - 1) / want;
-      const int splits = want == 1 ? 1 : (stages + chunk - 1) / chunk;
-      const float s = (float)((int64_t)chunk << c.lk) * (1.0f / 128);
+      const int64_t chunk = want == 1 ? stages : (stages - 1) / want + 1;
+      const int64_t splits = want == 1 ? 1 : (stages - 1) / chunk + 1;
+      const float s = (float)(chunk << c.lk) * (1.0f / 128);
       const int64_t nb = nt * splits;
       // workgroups per CU: between the mean and the busiest CU's
       const float mean = nb < kCus ? 1.0f : (float)nb * (1.0f / kCus);
@@ -683,7 +684,7 @@ static GemmPlan search_plan(int64_t M, int64_t N, int64_t K, int64_t max_exact_k
       if (splits > 1) cost += kSplitCost + split_out * (float)splits;
       if (best.splits == 0 || cost < best_cost) {
         best_cost = cost;
-        best = GemmPlan{(GemmTile)t, tiles_m, tiles_n, splits, (int64_t)chunk << c.lk};
+        best = GemmPlan{(GemmTile)t, tiles_m, tiles_n, (int)splits, chunk << c.lk};
       }
     };
     consider(1);
@@ -691,8 +692,8 @@ static GemmPlan search_plan(int64_t M, int64_t N, int64_t K, int64_t max_exact_k
     // and two of them alone do not cost more than there is to gain
     const float least = kSplitCost + 2 * split_out + c.fixed1;
     if (nt < kCus && stages > 1 && best_cost > least) {
-      for (int s = 2; s * nt < 2 * kCus && s <= stages; s *= 2) consider(s);
-      consider(kCus / (int)nt);
+      for (int64_t s = 2; s * nt < 2 * kCus && s <= stages; s *= 2) consider(s);
+      consider(kCus / nt);
     }
   }
   return best;

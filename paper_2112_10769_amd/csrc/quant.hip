@@ -145,9 +145,9 @@ __global__ __launch_bounds__(1024) void fold_partials_kernel(const uint32_t* __r
 //
 // When the transposed code layout is requested, work goes by tiles of
 // TW = 2^lt code words: TG = 2^lg column groups (8 columns each) by
-// TR = TW / TG rows.  TG is 32, or the next power of two above the number of
+// TR = TW / TG rows.  TG is 32 (16 for small tensors), or the next power of two above the number of
 // column groups for narrow matrices; TW is 4096 (LUQ) or 8192 (INT4), or
-// smaller (down to 1024) when that leaves too few tiles to fill the chip.
+// smaller (down to 1024 or 512) when that leaves too few tiles to fill the chip.
 //   Phase A: consecutive lanes take consecutive column groups of a row, so
 //            the loads and the row-major code stores of a row are contiguous;
 //            every 8-element code word also goes to LDS at [group][row].
@@ -948,7 +948,7 @@ static int encode_blocks_flat(int64_t n) {
 
 // Transposing tile shape: log2 of the column groups per tile (lg) and of the
 // code words per tile (lt).  Tiles shrink from 2^max_lt words until there are at
-// least three per compute unit (six for narrow matrices) or a tile is 1024
+// least three per compute unit (six for narrow matrices) or a tile is 2^min_lt
 // words (or 8 rows) small.
 struct TileShape {
   int lg, lt, blocks;

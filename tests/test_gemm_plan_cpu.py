@@ -1,0 +1,45 @@
+"""The GEMM planner, through the workspace it asks for (host only).
+
+A split plan asks for one [M][N] int32 slab per split, so the split count can be
+read back.  Every chunk's int32 sums must stay exact: |A| <= 64 and |B| <= 120 for
+the LUQ products (chunks up to 2^18), 120 * 120 for INT4 times INT4 (2^17).
+"""
+import random
+
+import pytest
+
+import paper_2112_10769_amd as luq
+
+
+def _splits(op, M, N, K):
+    d = (K, M, N) if op == luq.OP_GEMM_WGRAD else (M, N, K)
+    ws = luq.workspace_size(op, *d)
+    assert ws % (4 * M * N) == 0
+    return ws // (4 * M * N)
+
+
+@pytest.mark.parametrize("op,limit", [(luq.OP_GEMM_DGRAD, 1 << 18), (luq.OP_GEMM_WGRAD, 1 << 18),
+                                      (luq.OP_GEMM_FWD, 1 << 17)])
+def test_splits_keep_int32_sums_exact(op, limit):
+    rng = random.Random(3)
+    shapes = [(rng.randint(1, 9000), rng.randint(1, 9000), 32 * rng.randint(1, 60000)) for _ in range(400)]
+    shapes += [(m, n, k) for m in (1, 64, 8192) for n in (1, 576, 4096)
+               for k in (32, limit - 32, limit, limit + 32, 2 * limit, 2 * limit + 32, 5 * limit + 96)]
+    for M, N, K in shapes:
+        s = _splits(op, M, N, K)
+        assert s != 1, (M, N, K)                       # one split needs no workspace
+        assert s > 0 or K <= limit, (M, N, K, s)
+        if s:                                          # chunks are whole stages of at most 1024
+            assert -(-K // (s * 1024)) * 1024 <= limit and s <= -(-K // 128), (M, N, K, s)
+
+
+def test_few_tiles_split_and_many_do_not():
+    assert _splits(luq.OP_GEMM_WGRAD, 64, 576, 200704) > 1
+    assert _splits(luq.OP_GEMM_DGRAD, 8192, 4096, 16384) == 0
+    assert _splits(luq.OP_GEMM_DGRAD, 2048, 1024, 4096) == 0
+
+
+@pytest.mark.parametrize("d", [(1, 1, 1 << 40), (1 << 31, 1 << 31, 32), (1, 1, (1 << 62) + 5), (5, 7, 1)])
+def test_workspace_query_takes_any_sizes(d):
+    for op in (luq.OP_GEMM_DGRAD, luq.OP_GEMM_WGRAD, luq.OP_GEMM_FWD):
+        assert luq.workspace_size(op, *d) >= 0
