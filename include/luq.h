@@ -117,7 +117,8 @@ const char* luq_last_error(void);
  * ceil(n/2) rounded up to a multiple of 256. */
 size_t luq_plane_bytes(int64_t n);
 
-/* Device workspace (bytes) an operation needs; 0 if none.  The workspace
+/* Device workspace (bytes) an operation needs; 0 if none, or if its sizes are
+ * so large that the operation refuses them.  The workspace
  * holds per-block partial maxima and a status word (quantizers) or split-K
  * partial sums (GEMMs); its contents on entry do not matter. */
 size_t luq_workspace_size(int op, int64_t d0, int64_t d1, int64_t d2);

@@ -90,21 +90,27 @@ luq_status luq_query_status(const void* ws, void* stream) {
 
 size_t luq_plane_bytes(int64_t n) { return n <= 0 ? 0 : luq::plane_bytes(n); }
 
+// Sizes the GEMM planners take: every call beyond them is refused (gemm_shape), and
+// within them the tile counts neither overflow nor become 0.
+static bool gemm_sizes(int64_t M, int64_t N, int64_t K) {
+  return M > 0 && N > 0 && K > 0 && M <= INT32_MAX / 2 && N <= INT32_MAX / 2 && K <= INT32_MAX;
+}
+
 size_t luq_workspace_size(int op, int64_t d0, int64_t d1, int64_t d2) {
   switch (op) {
     case LUQ_OP_QUANTIZE_GRAD:
     case LUQ_OP_INT4_QUANTIZE:
       return d0 > 0 ? luq::quant_workspace_bytes(d0) : 0;
     case LUQ_OP_GEMM_DGRAD:
-      return (d0 > 0 && d1 > 0 && d2 > 0) ? luq::gemm_workspace_bytes(d0, d1, d2, 1) : 0;
+      return gemm_sizes(d0, d1, d2) ? luq::gemm_workspace_bytes(d0, d1, d2, 1) : 0;
     case LUQ_OP_GEMM_WGRAD:
-      return (d0 > 0 && d1 > 0 && d2 > 0) ? luq::gemm_workspace_bytes(d1, d2, d0, 1) : 0;
+      return gemm_sizes(d1, d2, d0) ? luq::gemm_workspace_bytes(d1, d2, d0, 1) : 0;
     case LUQ_OP_GEMM_FWD:
-      return (d0 > 0 && d1 > 0 && d2 > 0) ? luq::gemm_fwd_workspace_bytes(d0, d1, d2) : 0;
+      return gemm_sizes(d0, d1, d2) ? luq::gemm_fwd_workspace_bytes(d0, d1, d2) : 0;
     case LUQ_OP_GEMM_DGRAD_FP6:
-      return (d0 > 0 && d1 > 0 && d2 > 0) ? luq::gemm_fp6_workspace_bytes(d0, d1, d2) : 0;
+      return gemm_sizes(d0, d1, d2) && luq::gemm_fp6_fits(d0, d1, d2) ? luq::gemm_fp6_workspace_bytes(d0, d1, d2) : 0;
     case LUQ_OP_GEMM_WGRAD_FP6:
-      return (d0 > 0 && d1 > 0 && d2 > 0) ? luq::gemm_fp6_workspace_bytes(d1, d2, d0) : 0;
+      return gemm_sizes(d1, d2, d0) && luq::gemm_fp6_fits(d1, d2, d0) ? luq::gemm_fp6_workspace_bytes(d1, d2, d0) : 0;
     case LUQ_OP_CONV_WGRAD:
       return (d0 > 0 && d1 > 0 && d2 > 0 && d0 < ((int64_t)1 << 31) && d1 < ((int64_t)1 << 28) &&
               d2 < ((int64_t)1 << 28))

@@ -6,9 +6,7 @@
 namespace luq {
 
 size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int /*ns*/) {
-  const GemmPlan p = plan_gemm(M, N, K, kMaxExactK);
-  if (p.splits <= 1) return 0;
-  return (size_t)p.splits * (size_t)M * (size_t)N * sizeof(int32_t);
+  return split_bytes(plan_gemm(M, N, K, kMaxExactK), M, N);
 }
 
 hipError_t launch_gemm_luq_int4(const uint8_t* A, int64_t a_plane, int ns, const float* alpha,

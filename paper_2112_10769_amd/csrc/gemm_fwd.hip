@@ -7,9 +7,7 @@
 namespace luq {
 
 size_t gemm_fwd_workspace_bytes(int64_t M, int64_t N, int64_t K) {
-  const GemmPlan p = plan_gemm(M, N, K, kMaxExactKInt4);
-  if (p.splits <= 1) return 0;
-  return (size_t)p.splits * (size_t)M * (size_t)N * sizeof(int32_t);
+  return split_bytes(plan_gemm(M, N, K, kMaxExactKInt4), M, N);
 }
 
 hipError_t launch_gemm_int4_fwd(const uint8_t* X, const float* x_scale, int x_signed, const uint8_t* W,

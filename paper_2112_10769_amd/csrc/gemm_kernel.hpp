@@ -657,7 +657,8 @@ struct GemmPlan {
 
 // The tile and the number of splits with the least predicted time.  A split's k
 // range is a multiple of the tile's stage depth; min_splits keeps a chunk's int32
-// sums exact.
+// sums exact.  M, N <= 2^30 and K < 2^31 (checked at the entry points, the
+// workspace query among them), so no count overflows.
 static GemmPlan search_plan(int64_t M, int64_t N, int64_t K, int64_t max_exact_k) {
   GemmPlan best{};
   float best_cost = 0.0f;
@@ -665,7 +666,6 @@ static GemmPlan search_plan(int64_t M, int64_t N, int64_t K, int64_t max_exact_k
   const float split_out = kSplitCostPerMOut * 1e-6f * (float)M * (float)N;   // per split
   for (int t = 0; t < kGemmTiles; ++t) {
     const TileCost& c = kTileCost[t];
-    // (the workspace query takes any sizes: no overflow for v up to INT64_MAX)
     auto ceil_shift = [](int64_t v, int l) { return ((v - 1) >> l) + 1; };
     const int64_t tiles_m = ceil_shift(M, c.lm), tiles_n = ceil_shift(N, c.ln), nt = tiles_m * tiles_n;
     const int64_t stages = ceil_shift(K, c.lk);
@@ -711,6 +711,14 @@ static GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int64_t max_exact_k) 
   if (last.M != M || last.N != N || last.K != K || last.exact != max_exact_k)
     last = Last{M, N, K, max_exact_k, search_plan(M, N, K, max_exact_k)};
   return last.plan;
+}
+
+// Bytes of the plan's split sums; 0 without splits, and where they exceed any memory
+// (such operands are refused).
+static size_t split_bytes(const GemmPlan& p, int64_t M, int64_t N) {
+  size_t b = 0;
+  if (p.splits <= 1 || __builtin_mul_overflow((size_t)M * (size_t)N * sizeof(int32_t), (size_t)p.splits, &b)) return 0;
+  return b;
 }
 
 template <typename S, int AC, int NS, bool BSIGNED>

@@ -4,11 +4,17 @@ A split plan asks for one [M][N] int32 slab per split, so the split count can be
 read back.  Every chunk's int32 sums must stay exact: |A| <= 64 and |B| <= 120 for
 the LUQ products (chunks up to 2^18), 120 * 120 for INT4 times INT4 (2^17).
 """
+import json
+import os
 import random
+import subprocess
+import sys
 
 import pytest
 
 import paper_2112_10769_amd as luq
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 def _splits(op, M, N, K):
@@ -37,6 +43,34 @@ def test_few_tiles_split_and_many_do_not():
     assert _splits(luq.OP_GEMM_WGRAD, 64, 576, 200704) > 1
     assert _splits(luq.OP_GEMM_DGRAD, 8192, 4096, 16384) == 0
     assert _splits(luq.OP_GEMM_DGRAD, 2048, 1024, 4096) == 0
+
+
+GEMM_OPS = (luq.OP_GEMM_DGRAD, luq.OP_GEMM_WGRAD, luq.OP_GEMM_FWD, luq.OP_GEMM_DGRAD_FP6, luq.OP_GEMM_WGRAD_FP6)
+
+
+def _query(M, N, K):
+    """workspace_size of every GEMM, in a process of its own: a crash in it is one failure."""
+    args = [(op, K, M, N) if op in (luq.OP_GEMM_WGRAD, luq.OP_GEMM_WGRAD_FP6) else (op, M, N, K) for op in GEMM_OPS]
+    code = f"import paper_2112_10769_amd as l; print([l.workspace_size(*a) for a in {args}])"
+    res = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, cwd=ROOT)
+    assert res.returncode == 0, (M, N, K, res.returncode)
+    return json.loads(res.stdout.splitlines()[-1])
+
+
+# Sizes that every call refuses: tile counts that wrap to 0, split counts beyond 32
+# bits, operands and split sums beyond any address, and one past the query's limits.
+@pytest.mark.parametrize("M,N,K", [(1 << 40, 1 << 40, 1 << 20), (1 << 62, 1 << 62, 1 << 62), (1 << 36, 1 << 62, 1 << 36),
+                                   (5, 7, 1 << 55), (1, 1, (1 << 62) + 5), (5, 7, 1 << 31), (1 << 30, 7, 32),
+                                   ((1 << 30) - 1, (1 << 30) - 1, (1 << 31) - 1)])
+def test_workspace_query_of_refused_sizes_is_zero(M, N, K):
+    assert _query(M, N, K) == [0] * len(GEMM_OPS)
+
+
+def test_workspace_query_at_its_limits():
+    """The longest reduction a query plans for, K = 2^31 - 1."""
+    K = (1 << 31) - 1
+    for op, ws, limit in zip(GEMM_OPS, _query(5, 7, K), (1 << 18, 1 << 18, 1 << 17)):
+        assert ws % (4 * 35) == 0 and ws // (4 * 35) >= -(-K // limit), op
 
 
 @pytest.mark.parametrize("d", [(1, 1, 1 << 40), (1 << 31, 1 << 31, 32), (1, 1, (1 << 62) + 5), (5, 7, 1)])
