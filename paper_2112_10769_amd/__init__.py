@@ -93,16 +93,14 @@ def _check(status, where):
 # stream is asked for directly, and the workspace size only where the caller left
 # the workspace to the binding (five-call layer backward of 256 x 512 x 512: 47.9 ->
 # 36.4 us).
-_raw_stream = torch._C._cuda_getCurrentRawStream
-
-
 def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
 def _stream(dev):
     if dev.type == "cuda":
-        return _raw_stream(dev.index)
+        # looked up here: a CPU-only torch lacks it, and the host queries work there
+        return torch._C._cuda_getCurrentRawStream(dev.index)
     return torch.cuda.current_stream(dev).cuda_stream  # raises: not a GPU tensor
 
 

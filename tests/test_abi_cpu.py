@@ -7,6 +7,8 @@ pointers are never dereferenced.
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -45,6 +47,24 @@ def test_version_and_strings():
         assert LIB.luq_status_string(s)
     assert b"non-finite" in LIB.luq_status_string(8)
     assert LIB.luq_status_string(99) == b"unknown status"
+
+
+def test_host_queries_without_a_gpu_torch():
+    """A CPU-only torch has no raw stream query: the binding still imports there,
+    answers the host queries and refuses CPU tensors."""
+    code = """
+import torch
+if hasattr(torch._C, "_cuda_getCurrentRawStream"):
+    del torch._C._cuda_getCurrentRawStream
+import paper_2112_10769_amd as l
+assert l.plane_bytes(512) == 256 and l.workspace_size(l.OP_QUANTIZE_GRAD, 1000) > 0
+try:
+    l.int4_quantize(torch.zeros(8, 8))
+except Exception as e:
+    print("refused", type(e).__name__)
+"""
+    res = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, cwd=ROOT)
+    assert res.returncode == 0 and "refused" in res.stdout, res.stderr[-500:]
 
 
 def test_plane_and_workspace_sizes():
