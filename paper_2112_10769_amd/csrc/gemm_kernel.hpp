@@ -524,13 +524,16 @@ __global__ __launch_bounds__(S::THREADS, S::OCC) void gemm_tile_kernel(GemmArgs 
 // scales.  A block's 16 waves work on 16 / P runs of 256 outputs, P waves on
 // each: a lane adds every P-th chunk of four outputs (16-byte loads, eight in
 // flight), and with P > 1 the P partial sums meet in LDS.  Few waves per run
-// where there are many outputs, all of them where there are few (reduce_waves).
+// where there are many outputs, all of them where there are few
+// (launch_split_reduce).  The chunks are loaded 16 bytes a lane whatever the
+// alignment of out (vec: slabs of whole 16-byte groups); out is stored so only where
+// it is aligned itself.
 constexpr int kReduceThreads = 1024;
 
 template <int P, typename Scale>
 __global__ __launch_bounds__(kReduceThreads) void split_reduce_kernel(const int32_t* __restrict__ partial,
-                                                                     int splits, int64_t MN, int vec, Scale scale,
-                                                                     float* __restrict__ out) {
+                                                                     int splits, int64_t MN, int vec, int vec_out,
+                                                                     Scale scale, float* __restrict__ out) {
   constexpr int RUNS = kReduceThreads / 64 / P;
   __shared__ int64_t red[P > 1 ? kReduceThreads / 64 : 1][P > 1 ? 256 : 1];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -558,7 +561,7 @@ __global__ __launch_bounds__(kReduceThreads) void split_reduce_kernel(const int3
   }
   const float sc = scale();
   if constexpr (P == 1) {
-    if (vec && i0 + 3 < MN) {
+    if (vec_out && i0 + 3 < MN) {
       v4u v;
 #pragma unroll
       for (int k = 0; k < 4; ++k) v[k] = __float_as_uint(__fmul_rn((float)s[k], sc));
@@ -589,17 +592,17 @@ __global__ __launch_bounds__(kReduceThreads) void split_reduce_kernel(const int3
 template <typename Scale>
 static void launch_split_reduce(const int32_t* partial, int splits, int64_t MN, Scale scale, float* out,
                                 hipStream_t st) {
-  const int vec = MN % 4 == 0 && ((uintptr_t)out & 15) == 0;
+  const int vec = MN % 4 == 0, vec_out = vec && ((uintptr_t)out & 15) == 0;
   auto blocks = [&](int runs) { return dim3((unsigned)((MN + 256 * runs - 1) / (256 * runs))); };
   if (MN >= (1 << 19) || splits <= 4)
     hipLaunchKernelGGL((split_reduce_kernel<1, Scale>), blocks(16), dim3(kReduceThreads), 0, st, partial, splits, MN,
-                       vec, scale, out);
+                       vec, vec_out, scale, out);
   else if (MN >= (1 << 17) || splits <= 16)
     hipLaunchKernelGGL((split_reduce_kernel<4, Scale>), blocks(4), dim3(kReduceThreads), 0, st, partial, splits, MN,
-                       vec, scale, out);
+                       vec, vec_out, scale, out);
   else
     hipLaunchKernelGGL((split_reduce_kernel<16, Scale>), blocks(1), dim3(kReduceThreads), 0, st, partial, splits, MN,
-                       vec, scale, out);
+                       vec, vec_out, scale, out);
 }
 
 template <int AC, int NS, bool BSIGNED>
