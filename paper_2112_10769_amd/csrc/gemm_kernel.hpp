@@ -27,6 +27,8 @@
 // overflow; chunk sums are added in int64 in a fixed order.
 #pragma once
 
+#include <type_traits>
+
 #include "luq_device.hpp"
 #include "luq_launch.hpp"
 
@@ -520,89 +522,90 @@ __global__ __launch_bounds__(S::THREADS, S::OCC) void gemm_tile_kernel(GemmArgs 
   }
 }
 
-// Sums the split-K chunk sums in int64 in a fixed order and applies the
-// scales.  A block's 16 waves work on 16 / P runs of 256 outputs, P waves on
-// each: a lane adds every P-th chunk of four outputs (16-byte loads, eight in
-// flight), and with P > 1 the P partial sums meet in LDS.  Few waves per run
-// where there are many outputs, all of them where there are few
-// (launch_split_reduce).  The chunks are loaded 16 bytes a lane whatever the
-// alignment of out (vec: slabs of whole 16-byte groups); out is stored so only where
-// it is aligned itself.
-constexpr int kReduceThreads = 1024;
-
-template <int P, typename Scale>
-__global__ __launch_bounds__(kReduceThreads) void split_reduce_kernel(const int32_t* __restrict__ partial,
-                                                                     int splits, int64_t MN, int vec, int vec_out,
-                                                                     Scale scale, float* __restrict__ out) {
-  constexpr int RUNS = kReduceThreads / 64 / P;
-  __shared__ int64_t red[P > 1 ? kReduceThreads / 64 : 1][P > 1 ? 256 : 1];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int run = wave / P, part = wave % P;
-  const int64_t i0 = ((int64_t)blockIdx.x * RUNS + run) * 256 + 4 * lane;
-  int64_t s[4] = {0, 0, 0, 0};
-  if (vec && i0 + 3 < MN) {
-    for (int p0 = part; p0 < splits; p0 += 8 * P) {
-      v4i v[8];
+// Sums the split-K chunk sums in int64 in a fixed order and applies the scales.  A
+// wave takes a run of 64 W outputs, W a lane; P waves share a run (wave p adds every
+// P-th chunk, and with P > 1 their sums meet in LDS), RUNS runs make a workgroup.
+// Bound by latency below about 2^19 outputs (one output a lane spreads the few there
+// are over the most waves, and small workgroups start soonest) and by memory above it
+// (16 bytes a lane, 16 neighbouring runs per workgroup).  The chunk index is scalar,
+// so that the loads of a batch are issued without a test between them.  The chunks'
+// base is always 16-byte aligned; vec_out: so is out.
+template <int P, int RUNS, int W, typename Scale>
+__global__ __launch_bounds__(64 * P * RUNS) void split_reduce_kernel(const int32_t* __restrict__ partial, int splits,
+                                                                    int64_t MN, int vec_out, Scale scale,
+                                                                    float* __restrict__ out) {
+  static_assert(P == 1 || (W == 1 && RUNS == 1), "shared runs are one output a lane");
+  typedef int vw __attribute__((ext_vector_type(W)));
+  typedef float fw __attribute__((ext_vector_type(W)));
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int part = wave % P;
+  const int64_t i0 = ((int64_t)blockIdx.x * RUNS + wave / P) * 64 * W + W * lane;
+  const bool in = i0 < MN;   // MN is a multiple of W: a lane's outputs are in or out together
+  int64_t s[W];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int p = p0 + P * u;
-        v[u] = p < splits ? *reinterpret_cast<const v4i*>(partial + (int64_t)p * MN + i0) : v4i{0, 0, 0, 0};
-      }
+  for (int k = 0; k < W; ++k) s[k] = 0;
+  if (in) {
+    const int32_t* src = partial + i0;
+    int p = part;
+    auto batch = [&](auto u_) __attribute__((always_inline)) {
+      constexpr int U = decltype(u_)::value;
+      vw v[U];
 #pragma unroll
-      for (int u = 0; u < 8; ++u)
+      for (int u = 0; u < U; ++u) v[u] = *reinterpret_cast<const vw*>(src + (int64_t)(p + P * u) * MN);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) s[k] += v[u][k];
-    }
-  } else {
-    for (int p = part; p < splits; p += P)
+      for (int u = 0; u < U; ++u)
 #pragma unroll
-      for (int k = 0; k < 4; ++k)
-        if (i0 + k < MN) s[k] += partial[(int64_t)p * MN + i0 + k];
+        for (int k = 0; k < W; ++k) s[k] += v[u][k];
+      p += P * U;
+    };
+    while (p + 7 * P < splits) batch(std::integral_constant<int, 8>{});
+    if (p + 3 * P < splits) batch(std::integral_constant<int, 4>{});
+    if (p + P < splits) batch(std::integral_constant<int, 2>{});
+    if (p < splits) batch(std::integral_constant<int, 1>{});
   }
   const float sc = scale();
-  if constexpr (P == 1) {
-    if (vec_out && i0 + 3 < MN) {
-      v4u v;
+  if constexpr (P > 1) {
+    __shared__ int64_t red[P][64];
+    red[part][lane] = s[0];
+    __syncthreads();
+    if (part == 0 && in) {
 #pragma unroll
-      for (int k = 0; k < 4; ++k) v[k] = __float_as_uint(__fmul_rn((float)s[k], sc));
-      *reinterpret_cast<v4u*>(out + i0) = v;
+      for (int w = 1; w < P; ++w) s[0] += red[w][lane];
+      out[i0] = __fmul_rn((float)s[0], sc);
+    }
+  } else if (in) {
+    fw v;
+#pragma unroll
+    for (int k = 0; k < W; ++k) v[k] = __fmul_rn((float)s[k], sc);
+    if (W > 1 && vec_out) {
+      *reinterpret_cast<fw*>(out + i0) = v;
     } else {
 #pragma unroll
-      for (int k = 0; k < 4; ++k)
-        if (i0 + k < MN) out[i0 + k] = __fmul_rn((float)s[k], sc);
-    }
-  } else {
-#pragma unroll
-    for (int k = 0; k < 4; ++k) red[wave][4 * lane + k] = s[k];
-    __syncthreads();
-    for (int t = threadIdx.x; t < RUNS * 256; t += kReduceThreads) {
-      const int r = t >> 8;
-      const int64_t i = ((int64_t)blockIdx.x * RUNS + r) * 256 + (t & 255);
-      int64_t tot = 0;
-#pragma unroll
-      for (int w = 0; w < P; ++w) tot += red[r * P + w][t & 255];
-      if (i < MN) out[i] = __fmul_rn((float)tot, sc);
+      for (int k = 0; k < W; ++k) out[i0 + k] = v[k];
     }
   }
 }
 
-// out = scale * sum of `splits` chunk sums of MN outputs.  One wave per run of
-// 256 outputs when that already gives eight waves per CU (2^19 outputs) or
-// there are at most four chunks to add; 16 waves when there are few outputs.
+// out = scale * sum of `splits` chunk sums of MN outputs.  Timed alone over 64 to 2^22
+// outputs and 2 to 256 chunks (us): from 2^19 outputs of whole 16-byte groups on, W = 4
+// (2^20 outputs, 4 chunks: 3.4 against 3.7 with one output a lane and 6.5 with shared
+// runs; 2^21, 12: 17.4, 20.7, 20.5); below, one wave a run up to 24 chunks (55296
+// outputs, 16 chunks: 2.4 against 2.4 with four; 2^18, 16: 2.9 against 3.6) and four
+// waves beyond, or beyond 32 from 2^17 outputs on (1024 outputs, 128 chunks: 2.6
+// against 4.3; 55296, 64: 2.9 against 3.5).
 template <typename Scale>
 static void launch_split_reduce(const int32_t* partial, int splits, int64_t MN, Scale scale, float* out,
                                 hipStream_t st) {
-  const int vec = MN % 4 == 0, vec_out = vec && ((uintptr_t)out & 15) == 0;
-  auto blocks = [&](int runs) { return dim3((unsigned)((MN + 256 * runs - 1) / (256 * runs))); };
-  if (MN >= (1 << 19) || splits <= 4)
-    hipLaunchKernelGGL((split_reduce_kernel<1, Scale>), blocks(16), dim3(kReduceThreads), 0, st, partial, splits, MN,
-                       vec, vec_out, scale, out);
-  else if (MN >= (1 << 17) || splits <= 16)
-    hipLaunchKernelGGL((split_reduce_kernel<4, Scale>), blocks(4), dim3(kReduceThreads), 0, st, partial, splits, MN,
-                       vec, vec_out, scale, out);
+  auto launch = [&](auto kernel, int64_t outs, int threads, int vec_out) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((MN + outs - 1) / outs)), dim3(threads), 0, st, partial, splits, MN,
+                       vec_out, scale, out);
+  };
+  if (MN >= (1 << 19) && MN % 4 == 0 && splits <= 24)
+    launch(split_reduce_kernel<1, 16, 4, Scale>, 4096, 1024, ((uintptr_t)out & 15) == 0);
+  else if (splits <= (MN >= (1 << 17) ? 32 : 24))
+    launch(split_reduce_kernel<1, 4, 1, Scale>, 256, 256, 0);
   else
-    hipLaunchKernelGGL((split_reduce_kernel<16, Scale>), blocks(1), dim3(kReduceThreads), 0, st, partial, splits, MN,
-                       vec, vec_out, scale, out);
+    launch(split_reduce_kernel<4, 1, 1, Scale>, 64, 256, 0);
 }
 
 template <int AC, int NS, bool BSIGNED>
