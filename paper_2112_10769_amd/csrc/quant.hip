@@ -75,8 +75,12 @@ __device__ __forceinline__ uint32_t max_key8(const U8& v) {
 template <bool BF16, int MODE, bool NT>
 __global__ __launch_bounds__(kThreads) void max_partial_kernel(const void* __restrict__ x, int64_t n,
                                                               uint32_t* __restrict__ partial, int64_t keep) {
-  // groups of 8 elements per trip: eight 16-byte loads in flight per thread
-  constexpr int G = BF16 ? 8 : 4;
+  // Groups of 8 elements per trip, all in flight: eight 16-byte loads a thread where
+  // the tensor is streamed and memory bounds the pass; else latency does, and a trip
+  // is the four groups a thread of a small tensor has (with trips of eight, a bf16
+  // thread never filled one and loaded its four one by one: 2^20 bf16, whole
+  // quantizer, 6.3 -> 6.0 us, 9e6 15.7 -> 14.5).
+  constexpr int G = BF16 && NT ? 8 : 4;
   __shared__ uint32_t scratch[kThreads / kWave];
   const int64_t ngroups = n >> 3;
   const int64_t stride = (int64_t)gridDim.x * kThreads;
@@ -108,8 +112,18 @@ __global__ __launch_bounds__(kThreads) void max_partial_kernel(const void* __res
 #pragma unroll
       for (int e = 0; e < 8; ++e) m[i] = max(m[i], max_key<MODE>(v[i].v[e]));
   }
-  for (; g < ngroups; g += stride) {
-    const U8 a = load8<BF16>(x, g * 8);
+  // the last, partial trip is one batch too: an index past the end re-reads the last
+  // group, which leaves the maximum as it is (a single group is read alone)
+  if (g + stride < ngroups) {
+    U8 v[G];
+#pragma unroll
+    for (int i = 0; i < G; ++i) v[i] = load8<BF16, false>(x, min(g + i * stride, ngroups - 1) * 8);
+#pragma unroll
+    for (int i = 0; i < G; ++i)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) m[i] = max(m[i], max_key<MODE>(v[i].v[e]));
+  } else if (g < ngroups) {
+    const U8 a = load8<BF16, false>(x, g * 8);
 #pragma unroll
     for (int e = 0; e < 8; ++e) m[0] = max(m[0], max_key<MODE>(a.v[e]));
   }
@@ -919,9 +933,9 @@ __global__ __launch_bounds__(kThreads) void int4_small_kernel(Int4Args a, int lg
 
 // Every encode block folds the partials it is given before it starts, so
 // while they are given directly their count is kept proportional to the
-// tensor: four groups of 8 elements per max-pass thread for small tensors (256 x 512
-// fp32: 8.6 -> 8.0 us for the whole quantizer, 1184 x 1000: 10.7 -> 9.3), else
-// sixteen; large tensors get up to kMaxPartials blocks (8 groups per thread) and
+// tensor: four groups of 8 elements per max-pass thread, one trip, for small tensors
+// (256 x 512 fp32: 8.6 -> 8.0 us for the whole quantizer, 1184 x 1000: 10.7 -> 9.3),
+// else sixteen; large tensors get up to kMaxPartials blocks (8 groups per thread) and
 // one fold.
 static int max_pass_blocks(int64_t n, bool bf16) {
   const int64_t groups = (n + 7) >> 3;
