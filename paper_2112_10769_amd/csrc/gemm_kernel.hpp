@@ -117,7 +117,7 @@ struct GemmArgs {
   int32_t* partial;   // split-K chunk sums [splits][M][N], or null
   int64_t k_chunk;    // k per split (multiple of kKAlign)
   int tiles_m, tiles_n;
-  int vec;            // rows of C (or partial) are 16-byte aligned: vector stores
+  int vec;            // N % 4 == 0 and rows of C (or partial) are 16-byte aligned: vector stores
 };
 
 // Block -> output tile.  Blocks are dispatched round-robin over the 8 XCDs
@@ -463,11 +463,15 @@ __global__ __launch_bounds__(S::THREADS, S::OCC) void gemm_tile_kernel(GemmArgs 
   // registers 4q..4q+3, the 4 consecutive columns 8q + 4*(l/32) + 0..3.  Each
   // wave stages 32 rows of its block at a time as a row-major slab in its own
   // part of the (now idle) stage buffers, then stores whole row segments: LPR
-  // consecutive lanes cover one row of the block, RPI rows per instruction.  With
+  // consecutive lanes cover one row of the block, RPI rows per instruction, or,
+  // where rows are not 16-byte aligned, 4 bytes a lane on consecutive columns (four
+  // scalar stores a lane, 16 bytes apart, took the odd widths 1845 x 14329 over K = 128
+  // 52.5 against 23.1 us, 2655 x 2210 over 256 17.5 against 10.3).  With
   // KG > 1 the slabs hold the int32 sums and each k-group's wave stores 32 / KG of
   // the block's rows, adding the KG slabs of that block.  C gets the scaled fp32
   // values, the split-K workspace the raw int32 sums.
   constexpr int LPR = 8 * TN, RPI = 64 / LPR, SR = 32 / KG;
+  static_assert(TN <= 2 && SR % (2 / TN) == 0, "4-byte stores: whole rows per instruction");
   uint32_t* E = reinterpret_cast<uint32_t*>(lds) + wave * 32 * EP;
   const uint32_t* E0 = reinterpret_cast<const uint32_t*>(lds) + (wave % (S::WM * S::WN)) * 32 * EP;
   const bool part = a.partial != nullptr;
@@ -492,30 +496,62 @@ __global__ __launch_bounds__(S::THREADS, S::OCC) void gemm_tile_kernel(GemmArgs 
         *reinterpret_cast<v4u*>(E + (lane & 31) * EP + j * 32 + 8 * q + 4 * (lane >> 5)) = v;
       }
     __syncthreads();
+    if (a.vec) {
 #pragma unroll
-    for (int rr = 0; rr < SR; rr += RPI) {
-      const int sr = kg * SR + rr + srow;
-      const int64_t row = rbase + i * 32 + sr;
-      const int64_t col = cbase + scol;
-      if (row < a.M && (SR % RPI == 0 || rr + srow < SR)) {
-        v4u v = *reinterpret_cast<const v4u*>(E0 + sr * EP + scol);
+      for (int rr = 0; rr < SR; rr += RPI) {
+        const int sr = kg * SR + rr + srow;
+        const int64_t row = rbase + i * 32 + sr;
+        const int64_t col = cbase + scol;
+        if (row < a.M && col < a.N && (SR % RPI == 0 || rr + srow < SR)) {
+          v4u v = *reinterpret_cast<const v4u*>(E0 + sr * EP + scol);
+          if constexpr (KG > 1) {
+#pragma unroll
+            for (int g = 1; g < KG; ++g)
+              v += *reinterpret_cast<const v4u*>(E0 + (g * S::WM * S::WN * 32 + sr) * EP + scol);
+            if (!part) {
+#pragma unroll
+              for (int r = 0; r < 4; ++r) v[r] = __float_as_uint(__fmul_rn((float)(int32_t)v[r], sc));
+            }
+          }
+          *reinterpret_cast<v4u*>(out + row * a.N + col) = v;
+        }
+      }
+    } else if (cbase < a.N && rbase + i * 32 + kg * SR < a.M) {
+      // the LDS reads of a batch in flight together: 16 instructions where the block's
+      // rows all lie inside, else four, and none past M
+      constexpr int WC = 32 * TN, RS = 64 / WC, UA = SR < 16 * RS ? SR / RS : 16, UP = UA < 4 ? UA : 4;
+      int el = lane;
+      asm("" : "+v"(el));   // nothing of this path is computed before the loop
+      const int wrow = el / WC, wcol = el % WC;
+      const int64_t row0 = rbase + i * 32 + kg * SR, col = cbase + wcol;
+      const int inside = (int)min(a.M - row0, (int64_t)SR), rows = inside - wrow;   // the lane's rows
+      uint32_t* const dst = out + (row0 + wrow) * a.N + col;
+      const uint32_t* src = E0 + (kg * SR + wrow) * EP + wcol;
+      auto batch = [&](int rr, auto u_, auto whole) __attribute__((always_inline)) {
+        constexpr int U = decltype(u_)::value;
+        uint32_t v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = src[(rr + u * RS) * EP];
         if constexpr (KG > 1) {
 #pragma unroll
           for (int g = 1; g < KG; ++g)
-            v += *reinterpret_cast<const v4u*>(E0 + (g * S::WM * S::WN * 32 + sr) * EP + scol);
-          if (!part) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) v[r] = __float_as_uint(__fmul_rn((float)(int32_t)v[r], sc));
-          }
-        }
-        uint32_t* dst = out + row * a.N + col;
-        if (a.vec && col + 3 < a.N) {
-          *reinterpret_cast<v4u*>(dst) = v;
-        } else {
+            for (int u = 0; u < U; ++u) v[u] += src[(g * S::WM * S::WN * 32 + rr + u * RS) * EP];
 #pragma unroll
-          for (int r = 0; r < 4; ++r)
-            if (col + r < a.N) dst[r] = v[r];
+          for (int u = 0; u < U; ++u)
+            if (!part) v[u] = __float_as_uint(__fmul_rn((float)(int32_t)v[u], sc));
         }
+        uint32_t* const o = dst + rr * a.N;
+        if (col < a.N) {
+#pragma unroll
+          for (int u = 0; u < U; ++u)
+            if (decltype(whole)::value || rr + u * RS < rows) o[u * RS * a.N] = v[u];
+        }
+      };
+      if (inside == SR) {
+        for (int rr = 0; rr < SR; rr += UA * RS) batch(rr, std::integral_constant<int, UA>{}, std::true_type{});
+      } else {
+        for (int rr = 0; rr < inside; rr += UP * RS) batch(rr, std::integral_constant<int, UP>{}, std::false_type{});
       }
     }
     __syncthreads();  // the slab is rewritten by the next i

@@ -8,6 +8,7 @@ operand kind (LUQ, two planes, the int8 sums, INT4) runs on every shape.  Output
 are compared with the oracle within 1e-5 of sum |a b| and bit for bit with the
 fp32 epilogue applied to the exact integer sums.
 """
+import numpy as np
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -15,6 +16,7 @@ pytestmark = pytest.mark.gpu
 
 from test_gpu_parity import _gemm_case, _wgrad_case, _fwd_case  # noqa: E402
 from test_gpu_smp_sum import _dgrad_sum_case  # noqa: E402
+from gpu_util import announce, host  # noqa: E402
 
 
 @pytest.fixture(scope="module")
@@ -64,6 +66,28 @@ def test_tile_smp_sum(L, M, N, K):
 def test_tile_fwd(L, M, N, K, xsig):
     # an odd number of output columns: scalar stores
     _fwd_case(L, M, N - 3, K, xsig, True, seed=M + N + K + 3)
+
+
+@pytest.mark.parametrize("M,N,K", SHAPES)
+def test_tile_unaligned_output(L, M, N, K):
+    """Outputs only 4-byte aligned (dword stores, whole and partial row blocks): the same
+    values, and nothing written beside them.  One column and one row fewer in the second
+    pass: rows that are not multiples of 16 bytes."""
+    for m, n in ((M, N), (max(M - 1, 1), N - 1)):
+        announce("unaligned output", m, n, K)
+        gen = torch.Generator(device="cuda").manual_seed(m + n + K)
+        a, b = (torch.randint(256, (rows * K // 2,), dtype=torch.uint8, device="cuda", generator=gen) for rows in (m, n))
+        a &= 0x77
+        alpha, scale = torch.full((1,), 0.0123, device="cuda"), torch.full((1,), 0.37, device="cuda")
+        rows = -(-n // 4) * 4                      # the reference: the same product in rows of 16-byte multiples
+        wide = torch.zeros(rows * K // 2, dtype=torch.uint8, device="cuda")
+        wide[:b.numel()] = b
+        want = host(L.luq_gemm_dgrad(a, alpha, wide, scale, True, m, rows, K))[:, :n]
+        buf = torch.full((m * n + 8,), float("nan"), device="cuda")
+        L.luq_gemm_dgrad(a, alpha, b, scale, True, m, n, K, dx=buf[1:1 + m * n])
+        got = host(buf)
+        assert np.array_equal(got[1:1 + m * n].reshape(m, n), want)
+        assert np.isnan(got[:1]).all() and np.isnan(got[1 + m * n:]).all(), "wrote outside the output"
 
 
 @pytest.mark.parametrize("T,Nout,Kin", [(1056, 1064, 520), (65568, 72, 40), (96, 1032, 264)])
