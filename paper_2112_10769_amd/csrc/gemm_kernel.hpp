@@ -49,7 +49,6 @@ constexpr int kBufferFlags = 0x00020000;
 // A buffer offset beyond any operand's range: such loads return zeros.
 constexpr int kOutOfRange = 0x7FFFFFF0;
 
-constexpr int kKAlign = 128;            // k-chunk granularity of a split
 // int32-exact reduction lengths: |A| <= 64 (LUQ) or 120 (INT4 as 16q / 8q),
 // |B| <= 120: 2^18 * 7680 < 2^31 and 2^17 * 14400 < 2^31
 constexpr int64_t kMaxExactK = 1 << 18;
@@ -115,7 +114,7 @@ struct GemmArgs {
   const float* bscale;
   float* C;
   int32_t* partial;   // split-K chunk sums [splits][M][N], or null
-  int64_t k_chunk;    // k per split (multiple of kKAlign)
+  int64_t k_chunk;    // k per split (a multiple of the tile's stage depth)
   int tiles_m, tiles_n;
   int vec;            // N % 4 == 0 and rows of C (or partial) are 16-byte aligned: vector stores
 };
@@ -765,13 +764,20 @@ static size_t split_bytes(const GemmPlan& p, int64_t M, int64_t N) {
 
 template <typename S, int AC, int NS, bool BSIGNED>
 static void launch_tile(const GemmArgs& a, dim3 grid, hipStream_t st) {
-  // Prefetch depth by register budget (deeper modes spill where not taken): 256
-  // registers a wave for the 256x256 tile, 128 for most smaller ones, where one
-  // k-step ahead measured best.
+  // Prefetch depth, by what measured best; registers are 256 a wave for the two largest
+  // tiles and 128 for the others, and a deeper mode costs more of them.  256x256: the
+  // next stage's fragments too (PF 3), but for the int8 sums with unsigned B and two
+  // planes (PF 2: two planes spill 2 to 5 registers in either mode, and PF 1 took 8192 x
+  // 4096 over K = 16384 from 555 to 582 us).  With a partly filled last stage the k tests
+  // take registers: the int8 sums spilled 4 in PF 1 and none in PF 0 (4096 x 4096 over
+  // 1056: 32.1 -> 31.0 us).  64x64 with four k-groups, partial: PF 1 (up to 5 spilled in
+  // PF 2; 1024 x 512 over 4128, LUQ 11.6 -> 11.0 us, sums 10.1 -> 9.6), but for two planes
+  // (PF 2 16.5, PF 1 17.5).  Elsewhere one k-step ahead.
   constexpr bool kBig = S::BM == 256, kLuq1 = AC == kAcLuq && NS == 1, kLuq2 = AC == kAcLuq && NS == 2;
   constexpr int kSmall = S::BM == 64 && S::BN == 128 ? 1 : 2;
+  constexpr bool k64 = S::BM == 64 && S::BN == 64 && S::KG == 4;
   constexpr int kPfFull = !kBig ? kSmall : kLuq2 ? 2 : AC == kAcSum2 && !BSIGNED ? 2 : 3;
-  constexpr int kPfPart = !kBig ? kSmall : kLuq1 ? 2 : kLuq2 ? 0 : 1;
+  constexpr int kPfPart = !kBig ? (k64 && !kLuq2 ? 1 : kSmall) : kLuq1 ? 2 : kLuq2 || AC == kAcSum2 ? 0 : 1;
   if (a.K % S::BK == 0)
     hipLaunchKernelGGL((gemm_tile_kernel<AC, NS, BSIGNED, true, kPfFull, S>), grid, dim3(S::THREADS), 0, st, a);
   else
