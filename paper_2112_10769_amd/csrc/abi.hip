@@ -96,15 +96,22 @@ static bool gemm_sizes(int64_t M, int64_t N, int64_t K) {
   return M > 0 && N > 0 && K > 0 && M <= INT32_MAX / 2 && N <= INT32_MAX / 2 && K <= INT32_MAX;
 }
 
+// Two planes have a plan of their own, and the query does not say which it is for.
+static size_t gemm_workspace(int64_t M, int64_t N, int64_t K) {
+  if (!gemm_sizes(M, N, K)) return 0;
+  const size_t one = luq::gemm_workspace_bytes(M, N, K, 1), two = luq::gemm_workspace_bytes(M, N, K, 2);
+  return one > two ? one : two;
+}
+
 size_t luq_workspace_size(int op, int64_t d0, int64_t d1, int64_t d2) {
   switch (op) {
     case LUQ_OP_QUANTIZE_GRAD:
     case LUQ_OP_INT4_QUANTIZE:
       return d0 > 0 ? luq::quant_workspace_bytes(d0) : 0;
     case LUQ_OP_GEMM_DGRAD:
-      return gemm_sizes(d0, d1, d2) ? luq::gemm_workspace_bytes(d0, d1, d2, 1) : 0;
+      return gemm_workspace(d0, d1, d2);
     case LUQ_OP_GEMM_WGRAD:
-      return gemm_sizes(d1, d2, d0) ? luq::gemm_workspace_bytes(d1, d2, d0, 1) : 0;
+      return gemm_workspace(d1, d2, d0);
     case LUQ_OP_GEMM_FWD:
       return gemm_sizes(d0, d1, d2) ? luq::gemm_fwd_workspace_bytes(d0, d1, d2) : 0;
     case LUQ_OP_GEMM_DGRAD_FP6:

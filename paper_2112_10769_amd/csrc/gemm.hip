@@ -5,15 +5,17 @@
 
 namespace luq {
 
-size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int /*ns*/) {
-  return split_bytes(plan_gemm(M, N, K, kMaxExactK), M, N);
+static PlanKind plan_kind(int ns) { return ns == 2 ? kPlanTwoPlanes : kPlanOne; }
+
+size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int ns) {
+  return split_bytes(plan_gemm(M, N, K, kMaxExactK, plan_kind(ns)), M, N);
 }
 
 hipError_t launch_gemm_luq_int4(const uint8_t* A, int64_t a_plane, int ns, const float* alpha,
                                 const uint8_t* B, const float* bscale, int b_signed, int64_t M,
                                 int64_t N, int64_t K, float* C, void* ws, size_t /*ws_bytes*/,
                                 hipStream_t st) {
-  const GemmPlan p = plan_gemm(M, N, K, kMaxExactK);
+  const GemmPlan p = plan_gemm(M, N, K, kMaxExactK, plan_kind(ns));
   GemmArgs a;
   a.A = A;
   a.a_plane = a_plane;

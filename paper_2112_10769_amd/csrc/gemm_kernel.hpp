@@ -666,28 +666,61 @@ struct TileCost {
   float stage1, fixed1, stage, fixed;
 };
 
-// Least-squares fit to 1260 timings on an MI355X: 60 shapes (M and N from 1 to
-// 200704, K from 64 to 200704; LUQ, SMP sums and INT4 as the A operand), every
-// tile that covers them sensibly and 1 to 85 splits; the median deviation is 7%, and the
-// configuration with the least predicted time was within 1% (geometric mean) of
-// the best one measured, 17% at worst.  The former rule (256x256 tiles from 256
-// of them on, else 128x128 from 128 on, else 64x64, each with enough splits for
-// 512 workgroups) lost up to half on the shapes between: dX of 2048 x 1024 over K
-// = 4096 took 30.2 us as 128 tiles in four splits and takes 12.7 us as 256 tiles of
-// 64x128, because a split writes and reads back 4 bytes per output and chunk.
-constexpr TileCost kTileCost[kGemmTiles] = {
-    {8, 8, 7, 1.406f, 1.237f, 1.366f, 7.963f},  //
-    {7, 8, 7, 0.492f, 1.230f, 0.877f, 4.008f},  //
-    {7, 7, 7, 0.368f, 0.849f, 0.547f, 1.755f},  //
-    {6, 7, 8, 0.163f, 1.510f, 0.247f, 1.456f},   //
-    {6, 6, 9, 0.202f, 0.336f, 0.165f, 1.334f},    //
-    {5, 6, 9, 0.121f, 0.395f, 0.101f, 0.874f},    //
-    {5, 5, 10, 0.066f, 1.111f, 0.083f, 0.804f},   //
-    {6, 6, 7, 0.388f, 0.399f, 0.219f, 0.777f},
+// Operands a plan is for: one code of A per k (one LUQ plane, int8 sums, INT4), or two
+// LUQ planes, whose expansion takes twice the loads and three times the VALU work.
+enum PlanKind { kPlanOne, kPlanTwoPlanes, kPlanKinds };
+
+// Fitted to 73 000 timings on an MI355X: 1050 shapes drawn over M and N from 1 to 300000
+// and K from 32 to 262144 (a quarter short reductions, a quarter few outputs; odd sizes
+// among them), one LUQ plane, int8 sums, INT4 and two planes as the A operand, every
+// tile that covers a shape sensibly in 1 to 85 splits.  Minimised is the time that the
+// choice loses against the best one measured: 0.8 / 0.5% in the geometric mean (one code
+// per k / two planes), 5% at the 95th percentile, 27 / 19% at worst.  The former table,
+// one for all operands and fitted to the times alone, lost 2.4 / 4.2% on these shapes (14
+// / 29%, 43 / 72% at worst) and made short reductions of wide outputs and split products
+// of two planes slower than the tile rule before it (6912 x 3840 over 64 20.4 -> 23.4 us,
+// now 19.6; two planes of 128 x 64 over 6048 9.2 -> 11.8, now 6.4).
+constexpr TileCost kTileCost[kPlanKinds][kGemmTiles] = {
+    {
+        {8, 8, 7, 1.165f, 7.214f, 0.917f, 14.462f},
+        {7, 8, 7, 0.901f, 2.625f, 0.813f, 6.118f},
+        {7, 7, 7, 0.591f, 1.611f, 0.523f, 2.156f},
+        {6, 7, 8, 0.274f, 2.821f, 0.271f, 1.507f},
+        {6, 6, 9, 0.119f, 0.518f, 0.185f, 3.072f},
+        {5, 6, 9, 0.140f, 1.224f, 0.131f, 1.711f},
+        {5, 5, 10, 0.031f, 0.851f, 0.093f, 1.965f},
+        {6, 6, 7, 0.541f, 1.654f, 0.248f, 0.437f},
+    },
+    {
+        {8, 8, 7, 0.987f, 11.349f, 1.106f, 9.094f},
+        {7, 8, 7, 0.601f, 5.800f, 0.742f, 4.720f},
+        {7, 7, 7, 0.558f, 2.448f, 0.551f, 1.647f},
+        {6, 7, 8, 0.268f, 1.772f, 0.245f, 1.500f},
+        {},
+        {5, 6, 9, 0.139f, 0.706f, 0.121f, 0.846f},
+        {},
+        {6, 6, 7, 0.426f, 0.476f, 0.331f, 0.657f},
+    },
 };
-constexpr float kSplitCost = 3.4f;          // the reduction's launch
-constexpr float kSplitCostPerMOut = 1.12f;  // per 10^6 chunk sums written and read back
+struct SplitCost {
+  float launch;     // the reduction's launch
+  float per_mout;   // per 10^6 chunk sums written and read back
+};
+constexpr SplitCost kSplitCost[kPlanKinds] = {{2.664f, 2.120f}, {1.572f, 1.276f}};
+// Workgroups per CU: this far from the mean (0) to the busiest CU's (1).
+constexpr float kBusiest[kPlanKinds] = {0.760f, 1.000f};
+// Outputs beyond the 256 MB last-level cache leave at the rate of their row pieces: tiles
+// of 64 columns (256 bytes) take 1.05 to 1.5 times the 128-column tiles' time there, and
+// 0.87 to 1.2 times below (200704 x 576 over K = 64: 102 against 90 us).
+constexpr int64_t kCachedOutputs = 56 << 20;
+constexpr float kNarrowBeyondCache = 1.2f;
 constexpr int kCus = 256;
+
+// Two planes have no 64x64 and 32x32 tiles with k-groups: no shape was best on them by
+// more than 2%.
+constexpr bool tile_built(PlanKind kind, int t) {
+  return kind == kPlanOne || (t != kTile64x64 && t != kTile32x32);
+}
 
 struct GemmPlan {
   GemmTile tile;
@@ -698,15 +731,17 @@ struct GemmPlan {
 
 // The tile and the number of splits with the least predicted time.  A split's k
 // range is a multiple of the tile's stage depth; min_splits keeps a chunk's int32
-// sums exact.  M, N <= 2^30 and K < 2^31 (checked at the entry points, the
-// workspace query among them), so no count overflows.
-static GemmPlan search_plan(int64_t M, int64_t N, int64_t K, int64_t max_exact_k) {
+// sums exact; kind chooses the cost table.  M, N <= 2^30 and K < 2^31 (checked at the
+// entry points, the workspace query among them), so no count overflows.
+static GemmPlan search_plan(int64_t M, int64_t N, int64_t K, int64_t max_exact_k, PlanKind kind) {
   GemmPlan best{};
   float best_cost = 0.0f;
   const int64_t min_splits = K <= max_exact_k ? 1 : (K - 1) / max_exact_k + 1;
-  const float split_out = kSplitCostPerMOut * 1e-6f * (float)M * (float)N;   // per split
+  const SplitCost& sc = kSplitCost[kind];
+  const float split_out = sc.per_mout * 1e-6f * (float)M * (float)N;   // per split
   for (int t = 0; t < kGemmTiles; ++t) {
-    const TileCost& c = kTileCost[t];
+    if (!tile_built(kind, t)) continue;
+    const TileCost& c = kTileCost[kind][t];
     auto ceil_shift = [](int64_t v, int l) { return ((v - 1) >> l) + 1; };
     const int64_t tiles_m = ceil_shift(M, c.lm), tiles_n = ceil_shift(N, c.ln), nt = tiles_m * tiles_n;
     const int64_t stages = ceil_shift(K, c.lk);
@@ -717,12 +752,12 @@ static GemmPlan search_plan(int64_t M, int64_t N, int64_t K, int64_t max_exact_k
       const int64_t splits = want == 1 ? 1 : (stages - 1) / chunk + 1;
       const float s = (float)(chunk << c.lk) * (1.0f / 128);
       const int64_t nb = nt * splits;
-      // workgroups per CU: between the mean and the busiest CU's
       const float mean = nb < kCus ? 1.0f : (float)nb * (1.0f / kCus);
-      const float per_cu = 0.5f * (mean + (float)((nb + kCus - 1) / kCus));
+      const float per_cu = mean + kBusiest[kind] * ((float)((nb + kCus - 1) / kCus) - mean);
       const float alone = s * c.stage1 + c.fixed1, shared = per_cu * (s * c.stage + c.fixed);
       float cost = alone > shared ? alone : shared;
-      if (splits > 1) cost += kSplitCost + split_out * (float)splits;
+      if (M * N > kCachedOutputs && c.ln < 7) cost *= kNarrowBeyondCache;
+      if (splits > 1) cost += sc.launch + split_out * (float)splits;
       if (best.splits == 0 || cost < best_cost) {
         best_cost = cost;
         best = GemmPlan{(GemmTile)t, tiles_m, tiles_n, (int)splits, chunk << c.lk};
@@ -731,7 +766,7 @@ static GemmPlan search_plan(int64_t M, int64_t N, int64_t K, int64_t max_exact_k
     consider(1);
     // splits only where the tiles leave CUs idle (up to two workgroups per CU)
     // and two of them alone do not cost more than there is to gain
-    const float least = kSplitCost + 2 * split_out + c.fixed1;
+    const float least = sc.launch + 2 * split_out + c.fixed1;
     if (nt < kCus && stages > 1 && best_cost > least) {
       for (int64_t s = 2; s * nt < 2 * kCus && s <= stages; s *= 2) consider(s);
       consider(kCus / nt);
@@ -740,18 +775,19 @@ static GemmPlan search_plan(int64_t M, int64_t N, int64_t K, int64_t max_exact_k
   return best;
 }
 
-// The plan of the calling thread's last shape is kept: a call asks for it up to
-// three times (workspace size, its check, the launch), and the search costs 0.1 to
+// The plan of the calling thread's last shape of each kind is kept: a call asks for it
+// up to three times (workspace size, its check, the launch), and the search costs 0.1 to
 // 0.5 us of host time.
-static GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int64_t max_exact_k) {
+static GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int64_t max_exact_k, PlanKind kind = kPlanOne) {
   struct Last {
     int64_t M, N, K, exact;
     GemmPlan plan;
   };
-  static thread_local Last last{0, 0, 0, 0, {}};
-  if (last.M != M || last.N != N || last.K != K || last.exact != max_exact_k)
-    last = Last{M, N, K, max_exact_k, search_plan(M, N, K, max_exact_k)};
-  return last.plan;
+  static thread_local Last last[kPlanKinds]{};
+  Last& l = last[kind];
+  if (l.M != M || l.N != N || l.K != K || l.exact != max_exact_k)
+    l = Last{M, N, K, max_exact_k, search_plan(M, N, K, max_exact_k, kind)};
+  return l.plan;
 }
 
 // Bytes of the plan's split sums; 0 without splits, and where they exceed any memory
@@ -771,13 +807,13 @@ static void launch_tile(const GemmArgs& a, dim3 grid, hipStream_t st) {
   // 4096 over K = 16384 from 555 to 582 us).  With a partly filled last stage the k tests
   // take registers: the int8 sums spilled 4 in PF 1 and none in PF 0 (4096 x 4096 over
   // 1056: 32.1 -> 31.0 us).  64x64 with four k-groups, partial: PF 1 (up to 5 spilled in
-  // PF 2; 1024 x 512 over 4128, LUQ 11.6 -> 11.0 us, sums 10.1 -> 9.6), but for two planes
-  // (PF 2 16.5, PF 1 17.5).  Elsewhere one k-step ahead.
+  // PF 2; 1024 x 512 over 4128, LUQ 11.6 -> 11.0 us, sums 10.1 -> 9.6).  Elsewhere one
+  // k-step ahead.
   constexpr bool kBig = S::BM == 256, kLuq1 = AC == kAcLuq && NS == 1, kLuq2 = AC == kAcLuq && NS == 2;
   constexpr int kSmall = S::BM == 64 && S::BN == 128 ? 1 : 2;
-  constexpr bool k64 = S::BM == 64 && S::BN == 64 && S::KG == 4;
+  constexpr bool k64 = S::BM == 64 && S::BN == 64 && S::KG == 4;   // one code per k only
   constexpr int kPfFull = !kBig ? kSmall : kLuq2 ? 2 : AC == kAcSum2 && !BSIGNED ? 2 : 3;
-  constexpr int kPfPart = !kBig ? (k64 && !kLuq2 ? 1 : kSmall) : kLuq1 ? 2 : kLuq2 || AC == kAcSum2 ? 0 : 1;
+  constexpr int kPfPart = !kBig ? (k64 ? 1 : kSmall) : kLuq1 ? 2 : kLuq2 || AC == kAcSum2 ? 0 : 1;
   if (a.K % S::BK == 0)
     hipLaunchKernelGGL((gemm_tile_kernel<AC, NS, BSIGNED, true, kPfFull, S>), grid, dim3(S::THREADS), 0, st, a);
   else
@@ -793,14 +829,19 @@ static hipError_t gemm_launch_t(const GemmArgs& a0, const GemmPlan& p, hipStream
   const dim3 grid((unsigned)(p.tiles_m * p.tiles_n), (unsigned)p.splits);
   // 16-byte stores need 16-byte aligned rows
   a.vec = (a.N % 4) == 0 && (((uintptr_t)(a.partial ? (void*)a.partial : (void*)a.C)) & 15) == 0;
+  constexpr PlanKind kKind = AC == kAcLuq && NS == 2 ? kPlanTwoPlanes : kPlanOne;
   switch (p.tile) {
     case kTile256x256: launch_tile<Tile256x256, AC, NS, BSIGNED>(a, grid, st); break;
     case kTile128x256: launch_tile<Tile128x256, AC, NS, BSIGNED>(a, grid, st); break;
     case kTile128x128: launch_tile<Tile128x128, AC, NS, BSIGNED>(a, grid, st); break;
     case kTile64x128: launch_tile<Tile64x128, AC, NS, BSIGNED>(a, grid, st); break;
-    case kTile64x64: launch_tile<Tile64x64, AC, NS, BSIGNED>(a, grid, st); break;
+    case kTile64x64:
+      if constexpr (tile_built(kKind, kTile64x64)) launch_tile<Tile64x64, AC, NS, BSIGNED>(a, grid, st);
+      break;
     case kTile32x64: launch_tile<Tile32x64, AC, NS, BSIGNED>(a, grid, st); break;
-    case kTile32x32: launch_tile<Tile32x32, AC, NS, BSIGNED>(a, grid, st); break;
+    case kTile32x32:
+      if constexpr (tile_built(kKind, kTile32x32)) launch_tile<Tile32x32, AC, NS, BSIGNED>(a, grid, st);
+      break;
     default: launch_tile<Tile64x64k1, AC, NS, BSIGNED>(a, grid, st); break;
   }
   if (p.splits > 1)

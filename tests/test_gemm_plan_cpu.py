@@ -7,6 +7,7 @@ the LUQ products (chunks up to 2^18), 120 * 120 for INT4 times INT4 (2^17).
 import json
 import os
 import random
+import shutil
 import subprocess
 import sys
 
@@ -71,6 +72,73 @@ def test_workspace_query_at_its_limits():
     K = (1 << 31) - 1
     for op, ws, limit in zip(GEMM_OPS, _query(5, 7, K), (1 << 18, 1 << 18, 1 << 17)):
         assert ws % (4 * 35) == 0 and ws // (4 * 35) >= -(-K // limit), op
+
+
+# ---- which tile a shape gets ------------------------------------------------------
+
+PLAN = r"""
+#include <stdio.h>
+#include "gemm_kernel.hpp"
+int main() {
+  long M, N, K, exact;
+  int kind;
+  while (scanf("%ld %ld %ld %ld %d", &M, &N, &K, &exact, &kind) == 5) {
+    const luq::GemmPlan p = luq::search_plan(M, N, K, exact, (luq::PlanKind)kind);
+    printf("%d %d\n", (int)p.tile, p.splits);
+  }
+}
+"""
+TILES = ["256x256", "128x256", "128x128", "64x128", "64x64", "32x64", "32x32", "64x64k1"]
+DEPTH = dict(zip(TILES, (128, 128, 128, 256, 512, 512, 1024, 128)))
+
+
+@pytest.fixture(scope="module")
+def plans(tmp_path_factory):
+    """The planner compiled for the host: (M, N, K, exact limit, two planes) -> (tile, splits)."""
+    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+    if not os.path.exists(hipcc):
+        pytest.skip("no hipcc")
+    d = tmp_path_factory.mktemp("plan")
+    (d / "plan.hip").write_text(PLAN)
+    pkg = os.path.join(ROOT, "paper_2112_10769_amd", "csrc")
+    subprocess.run([hipcc, "--cuda-host-only", "-std=c++17", "-O1", "-I", pkg, "-I", os.path.join(ROOT, "include"),
+                    str(d / "plan.hip"), "-o", str(d / "plan")], check=True, capture_output=True)
+
+    def ask(shapes):
+        text = "\n".join(" ".join(str(int(v)) for v in s) for s in shapes)
+        out = subprocess.run([str(d / "plan")], input=text, check=True, capture_output=True, text=True).stdout
+        return [(TILES[int(t)], int(s)) for t, s in (line.split() for line in out.splitlines())]
+    return ask
+
+
+LIMITS = [(1 << 18, 0), (1 << 18, 1), (1 << 17, 0)]   # LUQ and the sums, two planes, INT4
+
+
+def test_tile_shapes_get_their_tiles(plans):
+    """The shapes of the per-tile GPU tests select the tiles that they name, and for every
+    operand kind each tile that it has is among them, on whole stages and on a partly
+    filled last one."""
+    from test_gpu_gemm_tiles import SHAPES, TILE_OF
+    got = plans([(*s, 1 << 18, 0) for s in SHAPES])
+    assert got == [TILE_OF[s] for s in SHAPES]
+    for limit in LIMITS:
+        kinds = {(t, s[2] % DEPTH[t] == 0) for s, (t, _) in zip(SHAPES, plans([(*s, *limit) for s in SHAPES]))}
+        tiles = [t for t in TILES[1:] if limit[1] == 0 or t not in ("64x64", "32x32")]
+        missing = {(t, w) for t in tiles for w in (True, False)} - kinds
+        assert not missing, (limit, missing)
+
+
+def test_query_covers_both_plans(plans):
+    """The workspace query answers for one plane, sums and two planes alike."""
+    rng = random.Random(5)
+    shapes = [(rng.randint(1, 3000), rng.randint(1, 3000), 32 * rng.randint(1, 4000)) for _ in range(300)]
+    one, two = (plans([(*s, 1 << 18, kind) for s in shapes]) for kind in (0, 1))
+    differ = 0
+    for s, (_, a), (_, b) in zip(shapes, one, two):
+        need = max(a if a > 1 else 0, b if b > 1 else 0)
+        assert _splits(luq.OP_GEMM_DGRAD, *s) == need, s
+        differ += a != b
+    assert differ, "the shapes do not tell the two plans apart"
 
 
 @pytest.mark.parametrize("d", [(1, 1, 1 << 40), (1 << 31, 1 << 31, 32), (1, 1, (1 << 62) + 5), (5, 7, 1)])

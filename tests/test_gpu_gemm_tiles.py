@@ -1,7 +1,8 @@
 """GPU parity of every GEMM tile shape through the C ABI.
 
 The planner picks a tile and a number of splits by predicted time; the shapes
-below select each tile, with M and N at and just past tile edges, K a multiple
+below select each tile but the largest, which has a file of its own
+(tests/test_gemm_plan_cpu.py checks that they do, without a GPU), with M and N at and just past tile edges, K a multiple
 of the tile's stage depth (whole stages) and not (the last stage partly past the
 end), one stage only, and split reductions whose last split is shorter.  Every A
 operand kind (LUQ, two planes, the int8 sums, INT4) runs on every shape.  Outputs
@@ -27,22 +28,29 @@ def L():
     return lib
 
 
-SHAPES = [
-    (4090, 4104, 2080),   # 256 x 256, half a stage left over
-    (4096, 2048, 1024),   # 128 x 256
-    (4099, 2056, 1120),   # 128 x 128
-    (2050, 1032, 544),    # 128 x 128, a quarter of a stage left over
-    (2048, 1024, 512),    # 64 x 128
-    (1060, 1032, 1056),   # 64 x 128, an eighth of a stage left over
-    (1024, 1024, 1024),   # 64 x 64, four k-groups
-    (200, 264, 1056),     # 32 x 64
-    (1, 64, 512),         # one row
-    (33, 200, 2080),      # 32 x 32, eight k-groups
-    (32, 64, 1024),       # 32 x 32, one stage
-    (520, 520, 96),       # 64 x 64, one k-group, less than a stage
-    (130, 264, 16416),    # 32 x 64, nine splits
-    (40, 72, 40000),      # 32 x 32, forty splits, the last one short
-]
+TILE_OF = {   # shape: the tile and the splits of a product of one code per k
+    (4090, 4104, 2080): ("128x128", 1),
+    (4096, 2048, 1024): ("128x256", 1),
+    (4099, 2056, 1120): ("128x128", 1),
+    (2050, 1032, 544): ("64x64k1", 1),
+    (2048, 1024, 512): ("64x64k1", 1),
+    (1060, 1032, 1056): ("64x128", 1),
+    (1024, 1024, 1024): ("64x64", 1),
+    (200, 264, 1056): ("32x64", 1),
+    (1, 64, 512): ("32x64", 1),
+    (33, 200, 2080): ("32x32", 1),
+    (32, 64, 1024): ("32x32", 1),
+    (520, 520, 96): ("64x64k1", 1),
+    (130, 264, 16416): ("32x64", 9),
+    (40, 72, 40000): ("32x32", 40),
+    (2050, 3576, 1056): ("128x256", 1),
+    (1060, 2072, 2048): ("64x128", 1),
+    (2050, 200, 1120): ("64x64", 1),
+    (2050, 1800, 128): ("128x128", 1),
+    (1024, 2560, 512): ("64x64k1", 1),
+    (33, 208, 4096): ("32x32", 1),
+}
+SHAPES = list(TILE_OF)
 
 
 @pytest.mark.parametrize("M,N,K", SHAPES)
