@@ -114,10 +114,17 @@ def plans(tmp_path_factory):
 LIMITS = [(1 << 18, 0), (1 << 18, 1), (1 << 17, 0)]   # LUQ and the sums, two planes, INT4
 
 
+def test_large_tile_shapes_get_the_large_tile(plans):
+    from test_gpu_gemm_large_tile import LARGE
+    for limit in LIMITS:
+        assert plans([(*s, *limit) for s in LARGE]) == [("256x256", 1)] * len(LARGE), limit
+    assert {K % 128 == 0 for _, _, K in LARGE} == {True, False}
+
+
 def test_tile_shapes_get_their_tiles(plans):
     """The shapes of the per-tile GPU tests select the tiles that they name, and for every
     operand kind each tile that it has is among them, on whole stages and on a partly
-    filled last one."""
+    filled last one (the largest tile: the test above)."""
     from test_gpu_gemm_tiles import SHAPES, TILE_OF
     got = plans([(*s, 1 << 18, 0) for s in SHAPES])
     assert got == [TILE_OF[s] for s in SHAPES]

@@ -223,7 +223,7 @@ def _gemm_case(L, M, N, K, ns, signed, seed):
 
 
 # shapes chosen to select each tile configuration (64x64 with and without
-# split-K, 128x128, 256x256) with ragged edges in M, N and K
+# split-K, larger ones) with ragged edges in M, N and K
 @pytest.mark.parametrize("M,N,K", [(256, 512, 512), (300, 200, 160), (37, 8, 32), (129, 136, 1056),
                                    (64, 64, 32768), (512, 384, 2048), (1500, 1400, 224),
                                    (4192, 4128, 288)])
@@ -266,8 +266,8 @@ def test_wgrad_signed_activations(L):
     _wgrad_case(L, 512, 64, 72, 1, signed=True, seed=9)
 
 
-# few output rows, long reduction: the 64x192 split-K tile (ragged and
-# 128-aligned reductions, ragged columns)
+# few output rows, long reduction: split reductions (ragged and 128-aligned
+# reductions, ragged columns)
 @pytest.mark.parametrize("T,Nout,Kin,ns", [(70048, 40, 200, 1), (66560, 64, 576, 1), (65696, 24, 392, 2)])
 def test_wgrad_wide_tile(L, T, Nout, Kin, ns):
     _wgrad_case(L, T, Nout, Kin, ns, signed=False, seed=T % 1000 + Kin)
@@ -301,8 +301,7 @@ def _fwd_case(L, M, N, K, xsig, wsig, seed, dtype=np.float32):
     assert np.array_equal(y, epilogue_replica(acc, rsx, 1, rsw)), "fwd epilogue not bit-exact"
 
 
-# every tile configuration (64x64 with and without split-K, 128x128 with
-# BK 64 and 128, 256x256, 64x192) with ragged M, N and K tails
+# small and large tiles, split and unsplit reductions, with ragged M, N and K tails
 @pytest.mark.parametrize("M,N,K", [(256, 512, 512), (300, 200, 160), (37, 8, 32), (129, 136, 1056),
                                    (64, 64, 32768), (512, 384, 2048), (1500, 1400, 224), (4192, 4128, 288),
                                    (2100, 1100, 64), (40, 200, 70048)])
