@@ -716,8 +716,9 @@ constexpr int64_t kCachedOutputs = 56 << 20;
 constexpr float kNarrowBeyondCache = 1.2f;
 constexpr int kCus = 256;
 
-// Two planes have no 64x64 and 32x32 tiles with k-groups: no shape was best on them by
-// more than 2%.
+// Two planes have no 64x64 and 32x32 tiles with k-groups: of 1050 shapes 8 were more than
+// 2% faster on them (5930 x 282 over 6528 by 7%, the most), and the cost table chose them
+// for next to none.
 constexpr bool tile_built(PlanKind kind, int t) {
   return kind == kPlanOne || (t != kTile64x64 && t != kTile32x32);
 }
